@@ -44,6 +44,22 @@ def test_quantize_e4m3_bit_exact(dist):
     assert np.array_equal(host(q), F.to_e4m3_bits(x, s_host))
 
 
+# 16384 and 32768 elements end the one-workgroup forms (16 and 32 elements a
+# thread), 4096 a workgroup's span of the two-kernel form; every remainder of
+# four, and a base off 16-byte alignment
+@pytest.mark.parametrize("off", [0, 1, 3])
+@pytest.mark.parametrize("count", [1, 2, 3, 5, 4095, 4097, 16384, 16385, 32767, 32768, 32769, 36866, 262147])
+def test_quantize_e4m3_every_form(count, off):
+    log(f"quantize e4m3 {count} elements at offset {off}")
+    x = synth.draw(synth.rng(count + off), (count + off,), "normal")
+    x[-1] *= np.float32(9.0)     # the maximum in the last group
+    d = dev(x)[off:]
+    q, s = mg.quantize_e4m3(d)
+    s_host = np.float32(host(s)[0])
+    assert s_host == F.e4m3_scale(x[off:])
+    assert np.array_equal(host(q), F.to_e4m3_bits(x[off:], s_host))
+
+
 def test_quantize_e4m3_zero_and_empty():
     log("quantize e4m3 zeros")
     q, s = mg.quantize_e4m3(dev(np.zeros((3, 5), np.float32)))
