@@ -33,6 +33,18 @@ def test_convert_bit_exact(mode, fmt):
     assert np.array_equal(got, want)
 
 
+# a workgroup converts 4096 elements in groups of four; every remainder of
+# four, and a base off 16-byte alignment
+@pytest.mark.parametrize("mode,fmt", [(1, "bf16"), (2, "f16")])
+@pytest.mark.parametrize("count,off", [(1, 0), (3, 1), (4095, 0), (4096, 2), (4097, 3), (8194, 1), (300003, 1)])
+def test_convert_group_edges(mode, fmt, count, off):
+    log(f"convert f32 -> {fmt}, {count} elements at offset {off}")
+    x = synth.draw(synth.rng(count), (count + off,), "wide")
+    got = host(mg.convert(dev(x)[off:], mode).view(torch.int16)).view(np.uint16)
+    want = F.to_bf16_bits(x[off:]) if fmt == "bf16" else F.to_f16_bits(x[off:])
+    assert np.array_equal(got, want)
+
+
 @pytest.mark.parametrize("dist", ["normal", "wide", "uniform"])
 def test_quantize_e4m3_bit_exact(dist):
     log(f"quantize e4m3 {dist}")
