@@ -178,22 +178,24 @@ int gemm_config_chunk(int32_t mode, int32_t cfg);
  * strides in elements.  Products and sums are binary64 operations on the
  * matrix cores (v_mfma_f64_16x16x4_f64); summation order is unspecified, so
  * each c_ij is within (k+2) 2^-53 (|A||B|)_ij of the exact value.  The tile
- * configuration is chosen from the shape; there is no split-K.  Same
+ * configuration is chosen from the shape, and with it whether the waves of a
+ * workgroup share out k (their partial sums are added in ascending k, in LDS):
+ * a shape gives the same bits whatever its strides.  No workspace.  Same
  * validation and errors as gemm_plain (C must not overlap A or B); k == 0
  * zeroes C. */
 int gemm_plain_f64(int64_t m, int64_t n, int64_t k, const double *A, int64_t lda, const double *B, int64_t ldb,
                    double *C, int64_t ldc, void *stream);
 /* As gemm_plain_f64 with an explicit configuration (gemm_config_info of
- * GEMM_MODE_F64; chunked configurations fall back as for gemm_plain_cfg, and
- * every configuration gives the same bits).  For tests. */
+ * GEMM_MODE_F64; chunked configurations fall back as for gemm_plain_cfg; k is
+ * not shared out, and every configuration gives the same bits).  For tests. */
 int gemm_plain_f64_cfg(int64_t m, int64_t n, int64_t k, const double *A, int64_t lda, const double *B,
                        int64_t ldb, double *C, int64_t ldc, int32_t cfg, void *stream);
 
 /* C = A*B over complex float: every element is an interleaved (re, im) pair
  * of float32 (8 bytes; C99 float _Complex layout), strides count COMPLEX
  * elements.  Each complex multiply-add is four real float32 MFMA products
- * (Re += ar br - ai bi, Im += ar bi + ai br) accumulated in float32.  No
- * split-K; same validation and errors as gemm_plain_f64. */
+ * (Re += ar br - ai bi, Im += ar bi + ai br) accumulated in float32.  Tile,
+ * sharing out of k, validation and errors as gemm_plain_f64. */
 int gemm_plain_c32(int64_t m, int64_t n, int64_t k, const float *A, int64_t lda, const float *B, int64_t ldb,
                    float *C, int64_t ldc, void *stream);
 int gemm_plain_c32_cfg(int64_t m, int64_t n, int64_t k, const float *A, int64_t lda, const float *B,

@@ -150,8 +150,10 @@ Launch make_launch(const gemm_problem_t &p, const KernelCfg &kc, int split) {
     P.scale = p.mode == GEMM_MODE_F8E4M3 ? p.scale_a * p.scale_b : 1.f;
     P.split_stride = ((int64_t)p.m * p.n + 3) / 4 * 4;
     L.splits = split;
-    L.nwg = P.tiles_m * P.tiles_n * split;
-    L.ws_bytes = split > 1 ? (int64_t)split * P.split_stride * 4 : 0;
+    // a fused configuration adds up to `fused` k ranges in its workgroup
+    const bool slabs = split > 1 && split > kc.fused;
+    L.nwg = P.tiles_m * P.tiles_n * (kc.fused ? (split + kc.fused - 1) / kc.fused : split);
+    L.ws_bytes = slabs ? (int64_t)split * P.split_stride * 4 : 0;
     return L;
 }
 
@@ -174,9 +176,22 @@ int effective_cfg(const gemm_problem_t &p, int cfg) {
     int count = 0;
     const KernelCfg *t = configs(p.mode, &count);
     if (!t || cfg < 0 || cfg >= count || cfg_eligible(p, t[cfg])) return cfg;
-    for (int c = 0; c < count; ++c)
-        if (t[c].chunk == 0 && !t[c].presplit && t[c].bm == t[cfg].bm && t[c].bn == t[cfg].bn) return c;
-    return 0;
+    // a fused configuration's k ranges stay in one launch where its tile size
+    // has an any-shape fused form
+    for (int fused = t[cfg].fused ? 1 : 0; fused >= 0; --fused)
+        for (int c = 0; c < count; ++c)
+            if (t[c].chunk == 0 && !t[c].presplit && (t[c].fused != 0) == (fused != 0) && t[c].bm == t[cfg].bm &&
+                t[c].bn == t[cfg].bn)
+                return c;
+    // no such tile size: the smallest larger one
+    int best = 0;
+    for (int c = 0; c < count; ++c) {
+        const int area = t[c].bm * t[c].bn;
+        if (t[c].chunk == 0 && !t[c].presplit && !t[c].fused && area >= t[cfg].bm * t[cfg].bn &&
+            area < t[best].bm * t[best].bn)
+            best = c;
+    }
+    return best;
 }
 
 // Bytes of the interleaved operand copies of the pre-split path (A' then B',
@@ -213,7 +228,8 @@ int enqueue_plain(const gemm_problem_t &p, int cfg, int split, void *ws, hipStre
     if (cfg < 0 || cfg >= count) return fail(GEMM_EINVAL, "config %d out of range [0,%d)", cfg, count);
     cfg = effective_cfg(p, cfg);
     Launch L = make_launch(p, t[cfg], split);
-    if (L.splits > 1) {
+    const bool slabs = L.ws_bytes > 0;
+    if (slabs) {
         if (!ws) return fail(GEMM_EINTERNAL, "split-K workspace missing");
         L.P.C = static_cast<float *>(ws);
     }
@@ -238,7 +254,7 @@ int enqueue_plain(const gemm_problem_t &p, int cfg, int split, void *ws, hipStre
         L.P.vec = 3;
     }
     MG_HIP(t[cfg].plain(L.P, L.nwg, s));
-    if (L.splits > 1)
+    if (slabs)
         MG_HIP(launch_splitk_reduce(static_cast<const float *>(ws), L.P.split_stride, L.splits, L.P.scale,
                                     p.C, p.ldc, (int)p.m, (int)p.n, s));
     return GEMM_OK;

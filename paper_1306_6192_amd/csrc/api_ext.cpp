@@ -1,6 +1,7 @@
 // C-ABI entry points of the binary64 and complex-float products and of the
 // element-wise matrix addition (plain launches, no split-K, no workspace).
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 
 #include "host.hpp"
@@ -38,9 +39,70 @@ static int validate_ext(int64_t m, int64_t n, int64_t k, const void *A, int64_t 
     return GEMM_OK;
 }
 
+// Choice of the tile of a binary64 or complex product, from its shape alone
+// (not from strides or alignment: the same shape always sums in the same
+// order).  A CU works through ceil(tiles / CUs) tiles of a configuration; one
+// takes its padded flops at the rate the family's large tiles sustain per CU
+// (binary64 73, complex 154 TFLOP/s over the chip), divided by the
+// configuration's relative rate, plus a fixed time for its first loads and its
+// store.  Both constants, and the lower rate of a four-wave 64x64 tile that
+// is alone on its CU, were fitted to the measured times of 28 shapes from 64^3
+// to 4096 x 4096 x 512, whole and ragged.  Against the 128x128 tiles
+// that every even shape ran on before (us): binary64 1024^3 123 -> 38, 1102 x
+// 128 x 3712 422 -> 37, 107 x 64 x 1344 156 -> 7; complex 1024^3 242 -> 76.
+struct ExtTile {
+    int cfg;
+    bool chunked;            // for whole 16-byte chunks of k and n only
+    double rate, rate_alone, tile_us;
+};
+
+static const ExtTile kF64Tiles[] = {
+    {2, true, 0.98, 0.98, 4.0},  {4, true, 0.95, 0.95, 1.0},  {6, true, 0.90, 0.90, 0.7},
+    {7, true, 0.85, 0.85, 0.9},  {8, true, 0.85, 0.85, 1.1},
+    {0, false, 0.75, 0.41, 4.0}, {1, false, 0.62, 0.31, 1.0}, {5, false, 0.75, 0.41, 1.0},
+    {9, false, 0.85, 0.85, 2.4}, {10, false, 0.60, 0.60, 1.8},
+};
+static const ExtTile kC32Tiles[] = {
+    {3, true, 0.93, 0.93, 2.0},  {5, true, 0.86, 0.80, 1.0},  {6, true, 0.80, 0.80, 1.0},
+    {0, false, 0.86, 0.50, 4.0}, {1, false, 0.80, 0.37, 1.0}, {7, false, 0.87, 0.87, 2.5},
+};
+
+static void ext_choose(int mode, int64_t m, int64_t n, int64_t k, int *cfg, int *split) {
+    *cfg = 0;
+    *split = 1;
+    if (m == 0 || n == 0 || k == 0) return;
+    const bool f64 = mode == GEMM_MODE_F64;
+    const ExtTile *tiles = f64 ? kF64Tiles : kC32Tiles;
+    const int nt = f64 ? (int)(sizeof(kF64Tiles) / sizeof(kF64Tiles[0])) : (int)(sizeof(kC32Tiles) / sizeof(kC32Tiles[0]));
+    int count = 0;
+    const KernelCfg *t = configs(mode, &count);
+    const bool whole = k % 2 == 0 && n % 2 == 0;
+    const double cus = num_cus();
+    const double cu_rate = (f64 ? 73.2e6 : 154.0e6) / 256.0;   // flop per microsecond per CU
+    const double flop_mac = f64 ? 2.0 : 8.0;
+    double best = 1e300;
+    for (int i = 0; i < nt; ++i) {
+        const ExtTile &e = tiles[i];
+        if (e.chunked != whole) continue;
+        const KernelCfg &kc = t[e.cfg];
+        const double rounds = std::ceil((double)((m + kc.bm - 1) / kc.bm) * (double)((n + kc.bn - 1) / kc.bn) / cus);
+        const int64_t nkt = (k + kc.bk - 1) / kc.bk;
+        const int sp = kc.fused ? (int)std::min<int64_t>(kc.fused, nkt) : 1;
+        // fewer k ranges than SIMDs leave SIMDs of the CU idle
+        const double idle = kc.fused && sp < 4 ? 4.0 / sp : 1.0;
+        const double work = flop_mac * kc.bm * kc.bn * (double)(nkt * kc.bk) / cu_rate * idle;
+        const double cost = rounds * (work / (rounds > 1 ? e.rate : e.rate_alone) + e.tile_us);
+        if (cost < best) {
+            best = cost;
+            *cfg = e.cfg;
+            *split = sp;
+        }
+    }
+}
+
 // One plain launch of configuration `cfg` of family `mode` (F64 or C32).
 static int enqueue_ext(int mode, int64_t m, int64_t n, int64_t k, const void *A, int64_t lda, const void *B,
-                       int64_t ldb, void *C, int64_t ldc, int cfg, hipStream_t s) {
+                       int64_t ldb, void *C, int64_t ldc, int cfg, int split, hipStream_t s) {
     const size_t es = 8;   // double, or a (re, im) float pair
     if (m == 0 || n == 0) return GEMM_OK;
     if (k == 0) {
@@ -67,6 +129,7 @@ static int enqueue_ext(int mode, int64_t m, int64_t n, int64_t k, const void *A,
         cfg = effective_cfg(p, cfg);
     }
     const KernelCfg &kc = t[cfg];
+    split = std::max(1, std::min(split, kc.fused));
     TileProblem P;
     memset(&P, 0, sizeof(P));
     P.A = A;
@@ -80,8 +143,12 @@ static int enqueue_ext(int mode, int64_t m, int64_t n, int64_t k, const void *A,
     P.k = (int32_t)k;
     P.tiles_m = (int32_t)((m + kc.bm - 1) / kc.bm);
     P.tiles_n = (int32_t)((n + kc.bn - 1) / kc.bn);
-    P.splits = 1;
-    P.kt_per_split = (int32_t)((k + kc.bk - 1) / kc.bk);
+    // k ranges of whole 16-k tiles (every configuration's k-tile), at most as
+    // many as a fused configuration adds in its workgroup: no slabs
+    const int64_t nkt = (k + kc.bk - 1) / kc.bk;
+    const int64_t per = (nkt + split - 1) / split;
+    P.splits = (int32_t)((nkt + per - 1) / per);
+    P.kt_per_split = (int32_t)per;
     P.scale = 1.f;
     const int64_t nwg = (int64_t)P.tiles_m * P.tiles_n;
     if (nwg > INT32_MAX) return fail(GEMM_EUNSUPPORTED, "too many output tiles");
@@ -93,11 +160,9 @@ static int plain_ext(int mode, int64_t m, int64_t n, int64_t k, const void *A, i
                      int64_t ldb, void *C, int64_t ldc, int cfg, void *stream) {
     int rc = validate_ext(m, n, k, A, lda, B, ldb, C, ldc, 8);
     if (rc != GEMM_OK) return rc;
-    if (cfg < 0) {
-        int split = 1;
-        tuner_choose(mode, m, n, k, &cfg, &split);
-    }
-    return enqueue_ext(mode, m, n, k, A, lda, B, ldb, C, ldc, cfg, (hipStream_t)stream);
+    int split = 1;
+    if (cfg < 0) ext_choose(mode, m, n, k, &cfg, &split);
+    return enqueue_ext(mode, m, n, k, A, lda, B, ldb, C, ldc, cfg, split, (hipStream_t)stream);
 }
 
 }  // namespace mg

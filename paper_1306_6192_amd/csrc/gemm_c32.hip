@@ -16,6 +16,12 @@ static const KernelCfg kC32Configs[] = {
     // 128x128: eight waves (64 x 32 each) and four waves (64 x 64 each)
     make_cfg<Lp2Cfg<GEMM_MODE_C32, 128, 128, 4, 2, 4>, 2, 2>(),
     make_cfg<Lp2Cfg<GEMM_MODE_C32, 128, 128, 4>, 1, 2>(),
+    // smaller tiles, for products whose 128x128 tiles would leave CUs idle:
+    // 64x64, and 32x32 with four waves along k (16-byte direct loads or, for
+    // any shape, loads through registers)
+    make_cfg<Lp2Cfg<GEMM_MODE_C32, 64, 64, 4>, 2, 2>(),
+    make_fused<Lp2Cfg<GEMM_MODE_C32, 32, 32, 2, 1, 1, 0, 16, 32, 4>, 2, 2>(),
+    make_fused<Lp2Cfg<GEMM_MODE_C32, 32, 32, 2, 1, 1, 0, 0, 32, 4>, 2>(),
 };
 
 const KernelCfg *c32_configs(int *count) {

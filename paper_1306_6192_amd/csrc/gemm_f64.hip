@@ -16,6 +16,18 @@ static const KernelCfg kF64Configs[] = {
     // eight waves (64 x 32 each) and four waves (64 x 64 each) on 128x128
     make_cfg<Lp2Cfg<GEMM_MODE_F64, 128, 128, 4, 2, 4>, 2, 2>(),
     make_cfg<Lp2Cfg<GEMM_MODE_F64, 128, 128, 4>, 1, 2>(),
+    // smaller tiles, for products whose 128x128 tiles would leave CUs idle:
+    // 64x64 (eight waves of 32x16; four waves with 4-byte direct loads for
+    // any shape) and 64x32
+    make_cfg<Lp2Cfg<GEMM_MODE_F64, 64, 64, 4, 2, 4>, 2, 2>(),
+    make_cfg<Lp2Cfg<GEMM_MODE_F64, 64, 64, 2, 2, 2, 0, 4>, 2>(),
+    make_cfg<Lp2Cfg<GEMM_MODE_F64, 64, 32, 4, 2, 2>, 2, 2>(),
+    // waves along k, 16-byte direct loads or (any shape) loads through
+    // registers: four on 32x32, eight on 16x16
+    make_fused<Lp2Cfg<GEMM_MODE_F64, 32, 32, 2, 1, 1, 0, 16, 32, 4>, 2, 2>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F64, 16, 16, 2, 1, 1, 0, 16, 32, 8>, 2, 2>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F64, 32, 32, 2, 1, 1, 0, 0, 32, 4>, 2>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F64, 16, 16, 2, 1, 1, 0, 0, 32, 8>, 2>(),
 };
 
 const KernelCfg *f64_configs(int *count) {

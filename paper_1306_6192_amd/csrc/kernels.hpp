@@ -42,6 +42,11 @@ struct KernelCfg {
     // and the product runs as one BF16 product over 3 x k16 (`plain` is then
     // a BF16 kernel).  Needs n a multiple of 8; any k, strides, alignment.
     int presplit;
+    // > 0: each of the workgroup's waves (this many) runs a k range of the
+    // split factor.  A factor up to that is added in LDS (no partial slabs,
+    // no reduction launch, the bits of both); the waves of a larger one write
+    // slabs.
+    int fused;
 };
 
 // The grouped kernel of a mode: the tile configurations its stream runs

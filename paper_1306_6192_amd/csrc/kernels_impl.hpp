@@ -65,5 +65,15 @@ template <class Cfg, int OCC, int CHUNK = 0, int PRESPLIT = 0>
 constexpr KernelCfg make_cfg() {
     return KernelCfg{Cfg::BM, Cfg::BN, Cfg::BK, Cfg::THREADS / 64, Cfg::LDS_BYTES, Cfg::MFMA_K,
                      (160 * 1024 / Cfg::LDS_BYTES) < OCC ? (160 * 1024 / Cfg::LDS_BYTES) : OCC,
-                     launch_plain_t<Cfg, OCC>, CHUNK, PRESPLIT};
+                     launch_plain_t<Cfg, OCC>, CHUNK, PRESPLIT, 0};
+}
+
+// The table entry of a tile whose waves run the k ranges of the split factor
+// (Lp2Cfg with WK).  OCC: waves per SIMD.
+template <class Cfg, int OCC, int CHUNK = 0>
+constexpr KernelCfg make_fused() {
+    return KernelCfg{Cfg::BM, Cfg::BN, Cfg::BK, Cfg::WK, Cfg::LDS_BYTES, Cfg::MFMA_K,
+                     (160 * 1024 / Cfg::LDS_BYTES) < 4 * OCC / Cfg::WK ? (160 * 1024 / Cfg::LDS_BYTES)
+                                                                       : (4 * OCC / Cfg::WK),
+                     launch_plain_t<Cfg, OCC>, CHUNK, 0, Cfg::WK};
 }

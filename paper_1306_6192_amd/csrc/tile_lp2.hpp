@@ -71,7 +71,8 @@ __device__ __forceinline__ void wait_vmcnt() {
 }
 
 // AROWB_: bytes of an A row per k-tile (0: the mode's own, 64 or 128).
-// LDB_: bytes each lane moves per direct load: 16 (global_load_lds_dwordx4;
+// LDB_: 0: loads through registers, any shape, stride and alignment (WK only).
+// Else the bytes each lane moves per direct load: 16 (global_load_lds_dwordx4;
 // k, n, strides and bases in whole 16-byte chunks) or 4 (FP32 only,
 // global_load_lds_dword: one element per lane, so any shape, stride and
 // alignment; the LDS image is the same, so are the bits).
@@ -79,14 +80,21 @@ __device__ __forceinline__ void wait_vmcnt() {
 // k-steps of 16) or 16 (v_mfma_f32_16x16x32, k-steps of 32; one such MFMA
 // gives the bits of two 32x32x16 MFMAs over its two k halves, so both tile
 // families of a mode give the same results).
+// WK_: waves along k (0: none).  Then one wave computes the whole BM x BN
+// tile (WM = WN = 1) over one of the k ranges of a split-K factor, from an
+// LDS ring of its own and without a barrier in its k loop, and the WK waves of
+// the workgroup add their partial sums in LDS, in ascending k range: the sum
+// the split-K slabs and their reduction launch give, without either.
 template <int MODE_, int BM_, int BN_, int STAGES_, int WM_ = 2, int WN_ = 2, int AROWB_ = 0, int LDB_ = 16,
-          int MB_ = 32>
+          int MB_ = 32, int WK_ = 0>
 struct Lp2Cfg {
     static constexpr int MODE = MODE_;
     static constexpr int BM = BM_, BN = BN_, STAGES = STAGES_;
     static constexpr int WM = WM_, WN = WN_;            // waves along m and n
-    static constexpr int WAVES = WM * WN;
-    static constexpr int THREADS = 64 * WAVES;
+    static constexpr int WAVES = WM * WN;               // waves that share a tile's loads
+    static constexpr int WK = WK_;
+    static_assert(WK == 0 || WAVES == 1, "a wave of a k range computes the whole tile");
+    static constexpr int THREADS = 64 * WAVES * (WK ? WK : 1);
     static constexpr bool F32 = (MODE == GEMM_MODE_F32);
     static constexpr bool F64 = (MODE == GEMM_MODE_F64);
     static constexpr bool C32 = (MODE == GEMM_MODE_C32);
@@ -117,10 +125,14 @@ struct Lp2Cfg {
     static constexpr int A_STAGE = BM * A_ROWB;
     static constexpr int B_STAGE = BK * B_ROWB;
     static constexpr int STAGE = A_STAGE + B_STAGE;
-    static constexpr int LDS_BYTES = STAGES * STAGE;
+    static constexpr int RING = STAGES * STAGE;         // LDS ring of the tile (of each wave with WK)
+    static constexpr int LDS_BYTES = RING * (WK ? WK : 1);
     static constexpr int LDB = LDB_;                    // bytes per lane per direct load
-    static constexpr int WLOAD = 64 * LDB;              // bytes one wave moves per direct load
-    static_assert(LDB == 16 || (LDB == 4 && F32), "16-byte loads, or 4-byte loads of float32 elements");
+    static constexpr bool REG = LDB == 0;               // 16-byte loads through registers
+    static_assert(!REG || (WK > 0 && STAGES == 2), "two register sets and two stages of a wave's own");
+    static constexpr int WLOAD = 64 * (REG ? 16 : LDB); // bytes one wave moves per load
+    static_assert(REG || LDB == 16 || (LDB == 4 && (F32 || F64 || C32)),
+                  "16-byte loads, or 4-byte loads of whole elements' words");
     static constexpr int A_LOADS = A_STAGE / WLOAD / WAVES;  // direct loads per wave per k-tile
     static constexpr int B_LOADS = B_STAGE / WLOAD / WAVES;
     static constexpr int LOADS = A_LOADS + B_LOADS;
@@ -179,6 +191,7 @@ struct Lp2Src {
     int ak[Cfg::A_LOADS];             // k of that chunk (element) within a k-tile
     const uint8_t *b[Cfg::B_LOADS];   // B row kr of the k-tile + column chunk (element)
     int bk[Cfg::B_LOADS];             // kr
+    int bcols[Cfg::REG ? Cfg::B_LOADS : 1];   // REG: matrix columns from that chunk on
     int64_t bstep;                    // bytes between consecutive B rows
     int kend;                         // loads at k >= kend read the zero chunk
     uint32_t dst_a, dst_b;            // this wave's first A / B destination in stage 0
@@ -188,10 +201,10 @@ template <class Cfg>
 __device__ __forceinline__ void lp2_sources(const TileProblem &P, int m0, int n0, int kend, const uint8_t *lds,
                                             Lp2Src<Cfg> &S) {
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(Cfg::WK ? 0 : threadIdx.x >> 6);
     const uint8_t *A = static_cast<const uint8_t *>(P.A);
     const uint8_t *B = static_cast<const uint8_t *>(P.B);
-    if constexpr (Cfg::LDB == 16) {
+    if constexpr (Cfg::LDB != 4) {
 #pragma unroll
         for (int j = 0; j < Cfg::A_LOADS; ++j) {
             const int t = wave * Cfg::A_LOADS + j;          // 1 KiB piece of the A stage
@@ -206,14 +219,16 @@ __device__ __forceinline__ void lp2_sources(const TileProblem &P, int m0, int n0
             const int slot = 64 * (wave * Cfg::B_LOADS + j) + lane;
             const int kr = slot / Cfg::B_CPR;
             const int c = (slot % Cfg::B_CPR) ^ Cfg::b_swz(kr);
-            const int n = min(n0 + c * Cfg::CE, P.n - Cfg::CE);
+            const int n = Cfg::REG ? n0 + c * Cfg::CE : min(n0 + c * Cfg::CE, P.n - Cfg::CE);
+            if constexpr (Cfg::REG) S.bcols[j] = P.n - n;
             S.bk[j] = kr;
             S.b[j] = B + ((int64_t)kr * P.ldb + n) * Cfg::ESZ;
         }
     } else {
         // 4-byte loads: lane L of load j writes stage byte WLOAD * (the wave's
-        // piece j) + 4 L, i.e. one element of a row's physical 16-byte chunk;
-        // it fetches that element of the logical chunk the swizzle puts there
+        // piece j) + 4 L, i.e. one element (or one of an 8-byte element's two
+        // words) of a row's physical 16-byte chunk; it fetches that word of
+        // the logical chunk the swizzle puts there
 #pragma unroll
         for (int j = 0; j < Cfg::A_LOADS; ++j) {
             const int byte = Cfg::WLOAD * (wave * Cfg::A_LOADS + j) + Cfg::LDB * lane;
@@ -222,7 +237,7 @@ __device__ __forceinline__ void lp2_sources(const TileProblem &P, int m0, int n0
             const int c = (o / 16) ^ Cfg::a_swz(r);                             // logical chunk
             const int row = min(m0 + r, P.m - 1);
             S.ak[j] = c * Cfg::CE + (o % 16) / Cfg::ESZ;
-            S.a[j] = A + ((int64_t)row * P.lda + S.ak[j]) * Cfg::ESZ;
+            S.a[j] = A + ((int64_t)row * P.lda + S.ak[j]) * Cfg::ESZ + o % Cfg::ESZ;
         }
 #pragma unroll
         for (int j = 0; j < Cfg::B_LOADS; ++j) {
@@ -233,7 +248,7 @@ __device__ __forceinline__ void lp2_sources(const TileProblem &P, int m0, int n0
             // columns past n: a valid element whose products are never stored
             const int n = min(n0 + c * Cfg::CE + (o % 16) / Cfg::ESZ, P.n - 1);
             S.bk[j] = kr;
-            S.b[j] = B + ((int64_t)kr * P.ldb + n) * Cfg::ESZ;
+            S.b[j] = B + ((int64_t)kr * P.ldb + n) * Cfg::ESZ + o % Cfg::ESZ;
         }
     }
     S.bstep = P.ldb * Cfg::ESZ;
@@ -267,6 +282,55 @@ template <class Cfg, bool CHECK = true>
 __device__ __forceinline__ void lp2_issue(const Lp2Src<Cfg> &S, int k0, uint32_t soff) {
 #pragma unroll
     for (int j = 0; j < Cfg::LOADS; ++j) lp2_issue_one<Cfg, CHECK>(S, k0, soff, j);
+}
+
+// The form without direct loads (REG): the same chunks, 16 bytes per lane from
+// any address, first into registers, then to the same places of the LDS image.
+// Chunks past the matrices' ends are not touched (zeros), chunks that end
+// inside one are read element by element; without CHECK the caller guarantees
+// that there are none.
+template <class Cfg>
+struct Lp2Reg {
+    u32x4 v[Cfg::LOADS];
+};
+
+// `have` elements of the chunk at p, zeros behind them.
+template <class Cfg>
+__device__ __forceinline__ u32x4 lp2_chunk(const uint8_t *p, int have) {
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (have >= Cfg::CE) {
+        v = ld16(p);
+    } else if (have > 0) {
+        uint8_t b[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) b[i] = 0;
+#pragma unroll
+        for (int e = 0; e < Cfg::CE; ++e)
+            if (e < have) __builtin_memcpy(b + e * Cfg::ESZ, p + e * Cfg::ESZ, Cfg::ESZ);
+        __builtin_memcpy(&v, b, 16);
+    }
+    return v;
+}
+
+template <class Cfg, bool CHECK>
+__device__ __forceinline__ void lp2_load(const Lp2Src<Cfg> &S, int k0, Lp2Reg<Cfg> &R) {
+#pragma unroll
+    for (int j = 0; j < Cfg::A_LOADS; ++j) {
+        const uint8_t *p = S.a[j] + (int64_t)k0 * Cfg::ESZ;
+        R.v[j] = CHECK ? lp2_chunk<Cfg>(p, S.kend - k0 - S.ak[j]) : ld16(p);
+    }
+#pragma unroll
+    for (int j = 0; j < Cfg::B_LOADS; ++j) {
+        const uint8_t *p = S.b[j] + (int64_t)k0 * S.bstep;
+        R.v[Cfg::A_LOADS + j] = CHECK ? lp2_chunk<Cfg>(p, k0 + S.bk[j] < S.kend ? S.bcols[j] : 0) : ld16(p);
+    }
+}
+
+template <class Cfg>
+__device__ __forceinline__ void lp2_land(const Lp2Reg<Cfg> &R, uint8_t *stage) {
+    uint8_t *dst = stage + 16 * (threadIdx.x & 63);
+#pragma unroll
+    for (int j = 0; j < Cfg::LOADS; ++j) *reinterpret_cast<u32x4 *>(dst + Cfg::WLOAD * j) = R.v[j];
 }
 
 // MFMA operand fragments of one k-step (KCH consecutive k) for the wave's
@@ -314,7 +378,7 @@ struct Lp2Frag<Cfg, 4> {
 template <class Cfg>
 __device__ __forceinline__ void lp2_read_piece(const uint8_t *stage, int kc, int p, Lp2Frag<Cfg> &F) {
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = Cfg::WK ? 0 : threadIdx.x >> 6;
     const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
     const int l32 = lane & 31, g = lane >> 5;
     const int p16 = lane & 15, G = lane >> 4;
@@ -561,21 +625,29 @@ __device__ __forceinline__ void lp2_epilogue(float *__restrict__ C, int64_t ldc,
 template <class Cfg, bool BOUNDARY, bool CHECK>
 __device__ __forceinline__ void lp2_step(const Lp2Src<Cfg> &S, int kt0, int i, int u, int kc, uint8_t *lds,
                                          const Lp2Frag<Cfg> &cur, Lp2Frag<Cfg> &nxt,
-                                         typename Cfg::Acc (&acc)[Cfg::RB][Cfg::CBA]) {
+                                         typename Cfg::Acc (&acc)[Cfg::RB][Cfg::CBA], Lp2Reg<Cfg> *reg) {
     constexpr int NP = Cfg::NP;                     // fragment pieces per step
     constexpr int NM = Cfg::NM;                     // MFMAs per step
     if constexpr (BOUNDARY) {
         // MFMAs before the barrier
-        constexpr int H = Cfg::FOUR ? NM / 2 : ((Cfg::RB + 1) / 2) * Cfg::CB;
-        constexpr int W = NP + Cfg::LOADS;                 // work items after it
+        constexpr int H = Cfg::FOUR || Cfg::RB == 1 ? NM / 2 : ((Cfg::RB + 1) / 2) * Cfg::CB;
+        constexpr int W = NP + (Cfg::REG ? 0 : Cfg::LOADS);   // work items after it
         constexpr int PER = (W + (NM - H) - 1) / (NM - H);
         static_assert(H < NM && (NM - H) * PER >= W, "every read and refill load is issued");
 #pragma unroll
         for (int t = 0; t < H; ++t) lp2_mfma1<Cfg>(cur, acc, t);
         __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        wait_vmcnt<(Cfg::STAGES - 2) * Cfg::LOADS>();
-        __syncthreads();
+        if constexpr (Cfg::REG) {
+            // k-tile i + 1 from its registers to the other stage, whose
+            // readers (this wave) are done; k-tile i + 3 into the registers
+            lp2_land<Cfg>(reg[(u + 1) % 2], lds + ((u + 1) % 2) * Cfg::STAGE);
+            lp2_load<Cfg, CHECK>(S, (kt0 + i + 3) * Cfg::BK, reg[(u + 1) % 2]);
+        } else {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            wait_vmcnt<(Cfg::STAGES - 2) * Cfg::LOADS>();
+        }
+        if constexpr (Cfg::WK) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // a ring of its own
+        else __syncthreads();
         const uint8_t *next = lds + ((u + 1) % Cfg::STAGES) * Cfg::STAGE;
         const int k0 = (kt0 + i + Cfg::STAGES) * Cfg::BK;
 #pragma unroll
@@ -617,17 +689,17 @@ __device__ __forceinline__ void lp2_step(const Lp2Src<Cfg> &S, int kt0, int i, i
 // number of steps per k-tile) or in `fb` (one step).
 template <class Cfg, bool CHECK>
 __device__ __forceinline__ void lp2_ktile(const Lp2Src<Cfg> &S, int kt0, int i, int u, uint8_t *lds,
-                                          Lp2Frag<Cfg> &fa, Lp2Frag<Cfg> &fb, typename Cfg::Acc (&acc)[Cfg::RB][Cfg::CBA]) {
+                                          Lp2Frag<Cfg> &fa, Lp2Frag<Cfg> &fb, typename Cfg::Acc (&acc)[Cfg::RB][Cfg::CBA], Lp2Reg<Cfg> *reg) {
     if constexpr (Cfg::STEPS == 1) {
-        lp2_step<Cfg, true, CHECK>(S, kt0, i, u, 0, lds, fa, fb, acc);
+        lp2_step<Cfg, true, CHECK>(S, kt0, i, u, 0, lds, fa, fb, acc, reg);
     } else {
 #pragma unroll
         for (int kc = 0; kc + 2 < Cfg::STEPS; kc += 2) {
-            lp2_step<Cfg, false, CHECK>(S, kt0, i, u, kc, lds, fa, fb, acc);
-            lp2_step<Cfg, false, CHECK>(S, kt0, i, u, kc + 1, lds, fb, fa, acc);
+            lp2_step<Cfg, false, CHECK>(S, kt0, i, u, kc, lds, fa, fb, acc, reg);
+            lp2_step<Cfg, false, CHECK>(S, kt0, i, u, kc + 1, lds, fb, fa, acc, reg);
         }
-        lp2_step<Cfg, false, CHECK>(S, kt0, i, u, Cfg::STEPS - 2, lds, fa, fb, acc);
-        lp2_step<Cfg, true, CHECK>(S, kt0, i, u, Cfg::STEPS - 1, lds, fb, fa, acc);
+        lp2_step<Cfg, false, CHECK>(S, kt0, i, u, Cfg::STEPS - 2, lds, fa, fb, acc, reg);
+        lp2_step<Cfg, true, CHECK>(S, kt0, i, u, Cfg::STEPS - 1, lds, fb, fa, acc, reg);
     }
 }
 
@@ -636,19 +708,25 @@ __device__ __forceinline__ void lp2_ktile(const Lp2Src<Cfg> &S, int kt0, int i, 
 template <class Cfg, bool CHECK>
 __device__ __forceinline__ void lp2_pair(const Lp2Src<Cfg> &S, int kt0, int i, int u, int nt, bool guard,
                                          uint8_t *lds, Lp2Frag<Cfg> &f0, Lp2Frag<Cfg> &f1,
-                                         typename Cfg::Acc (&acc)[Cfg::RB][Cfg::CBA]) {
-    if (!guard || i < nt) lp2_ktile<Cfg, CHECK>(S, kt0, i, u, lds, f0, f1, acc);
+                                         typename Cfg::Acc (&acc)[Cfg::RB][Cfg::CBA], Lp2Reg<Cfg> *reg) {
+    if (!guard || i < nt) lp2_ktile<Cfg, CHECK>(S, kt0, i, u, lds, f0, f1, acc, reg);
     if (!guard || i + 1 < nt) {
-        if constexpr (Cfg::STEPS % 2 == 0) lp2_ktile<Cfg, CHECK>(S, kt0, i + 1, u + 1, lds, f0, f1, acc);
-        else lp2_ktile<Cfg, CHECK>(S, kt0, i + 1, u + 1, lds, f1, f0, acc);
+        if constexpr (Cfg::STEPS % 2 == 0) lp2_ktile<Cfg, CHECK>(S, kt0, i + 1, u + 1, lds, f0, f1, acc, reg);
+        else lp2_ktile<Cfg, CHECK>(S, kt0, i + 1, u + 1, lds, f1, f0, acc, reg);
     }
 }
 
+// The tile's products over k range `split`, through the LDS ring at `lds`;
+// stored to C or the range's slab, or (WK) left in LDS for lp2_tile_wk.
 template <class Cfg>
 __device__ __forceinline__ void lp2_tile(const TileProblem &P, int tm, int tn, int split, uint8_t *lds) {
     static_assert(Cfg::STEPS == 1 || Cfg::STEPS % 2 == 0, "pipeline written for 1 or an even number of steps per k-tile");
     static_assert(Cfg::STAGES % 2 == 0, "k-tiles are processed in pairs of stages");
-    const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
+    // (REG: the last column tile is moved left, so that its rows are whole
+    // 16-byte chunks where the matrix has BN columns; lp2_tile_wk stores only
+    // the columns that are the tile's own)
+    const int m0 = tm * Cfg::BM;
+    const int n0 = Cfg::REG ? max(0, min(tn * Cfg::BN, P.n - Cfg::BN)) : tn * Cfg::BN;
     const int nkt = (P.k + Cfg::BK - 1) / Cfg::BK;
     const int kt0 = split * P.kt_per_split;
     const int kt1 = min(kt0 + P.kt_per_split, nkt);
@@ -670,11 +748,23 @@ __device__ __forceinline__ void lp2_tile(const TileProblem &P, int tm, int tn, i
         const int kend = min(P.k, kt1 * Cfg::BK);
         lp2_sources<Cfg>(P, m0, n0, kend, lds, S);
         // k-tiles [0, nfull) of this split lie wholly before kend
-        const int nfull = (kend - kt0 * Cfg::BK) / Cfg::BK;
+        int nfull = (kend - kt0 * Cfg::BK) / Cfg::BK;
+        Lp2Reg<Cfg> reg_sets[Cfg::REG ? 2 : 1];
+        Lp2Reg<Cfg> *reg = reg_sets;
+        if constexpr (Cfg::REG) {
+            // k-tile 0 to stage 0, k-tiles 1 and 2 in the registers
+            if (P.n - n0 < Cfg::BN) nfull = 0;     // chunks that end past the last column
+            lp2_load<Cfg, true>(S, kt0 * Cfg::BK, reg[0]);
+            lp2_load<Cfg, true>(S, (kt0 + 1) * Cfg::BK, reg[1]);
+            lp2_land<Cfg>(reg[0], lds);
+            lp2_load<Cfg, true>(S, (kt0 + 2) * Cfg::BK, reg[0]);
+        } else {
 #pragma unroll
-        for (int s = 0; s < Cfg::STAGES; ++s) lp2_issue<Cfg>(S, (kt0 + s) * Cfg::BK, s * Cfg::STAGE);
-        wait_vmcnt<(Cfg::STAGES - 1) * Cfg::LOADS>();
-        __syncthreads();
+            for (int s = 0; s < Cfg::STAGES; ++s) lp2_issue<Cfg>(S, (kt0 + s) * Cfg::BK, s * Cfg::STAGE);
+            wait_vmcnt<(Cfg::STAGES - 1) * Cfg::LOADS>();
+        }
+        if constexpr (Cfg::WK) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // a ring of its own
+        else __syncthreads();
         Lp2Frag<Cfg> f0, f1;
         lp2_read<Cfg>(lds, 0, f0);
         int i = 0;
@@ -682,20 +772,34 @@ __device__ __forceinline__ void lp2_tile(const TileProblem &P, int tm, int tn, i
         // whole: no k bound on the loads
         // (the stage loops are written out here: behind a helper function
         // the compiler unrolls them less and the eight-wave FP32 tiles spill)
-        for (; i + 2 * Cfg::STAGES <= nfull; i += Cfg::STAGES) {
+        // (REG loads k-tiles i + 3 and i + 4 in such a round)
+        for (; i + 2 * Cfg::STAGES + (Cfg::REG ? 1 : 0) <= nfull; i += Cfg::STAGES) {
 #pragma unroll
             for (int u = 0; u < Cfg::STAGES; u += 2)
-                lp2_pair<Cfg, false>(S, kt0, i + u, u, nt, false, lds, f0, f1, acc);
+                lp2_pair<Cfg, false>(S, kt0, i + u, u, nt, false, lds, f0, f1, acc, reg);
         }
         for (; i + Cfg::STAGES <= nt; i += Cfg::STAGES) {
 #pragma unroll
             for (int u = 0; u < Cfg::STAGES; u += 2)
-                lp2_pair<Cfg, true>(S, kt0, i + u, u, nt, false, lds, f0, f1, acc);
+                lp2_pair<Cfg, true>(S, kt0, i + u, u, nt, false, lds, f0, f1, acc, reg);
         }
         // the last nt mod STAGES k-tiles (stages 0 ..)
 #pragma unroll
-        for (int u = 0; u < Cfg::STAGES; u += 2) lp2_pair<Cfg, true>(S, kt0, i + u, u, nt, true, lds, f0, f1, acc);
-        wait_vmcnt<0>();   // the loads past the end have landed before the ring is reused
+        for (int u = 0; u < Cfg::STAGES; u += 2) lp2_pair<Cfg, true>(S, kt0, i + u, u, nt, true, lds, f0, f1, acc, reg);
+        if constexpr (!Cfg::REG) wait_vmcnt<0>();   // the loads past the end have landed before the ring is reused
+    }
+    if constexpr (Cfg::WK) {
+        // accumulator register q of lane l at element 64 q + l of this wave's ring
+        typedef typename std::conditional<Cfg::F64, double, float>::type E;
+        E *part = reinterpret_cast<E *>(lds) + (threadIdx.x & 63);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the ring's last reads
+#pragma unroll
+        for (int rb = 0; rb < Cfg::RB; ++rb)
+#pragma unroll
+            for (int cb = 0; cb < Cfg::CBA; ++cb)
+#pragma unroll
+                for (int r = 0; r < NACC; ++r) part[((rb * Cfg::CBA + cb) * NACC + r) * 64] = acc[rb][cb][r];
+        return;
     }
     __syncthreads();       // the LDS ring may be refilled by this workgroup's next tile
     if constexpr (Cfg::F64) {
@@ -716,9 +820,92 @@ __device__ __forceinline__ void lp2_tile(const TileProblem &P, int tm, int tn, i
     }
 }
 
-template <int MODE, int BM, int BN, int STAGES, int WM, int WN, int AROWB, int LDB, int MB>
-__device__ __forceinline__ void Lp2Cfg<MODE, BM, BN, STAGES, WM, WN, AROWB, LDB, MB>::run(const TileProblem &P,
-                                                                                    int tm, int tn, int split,
-                                                                                    uint8_t *lds) {
-    lp2_tile<Lp2Cfg<MODE, BM, BN, STAGES, WM, WN, AROWB, LDB, MB>>(P, tm, tn, split, lds);
+// Where accumulator register q (row block, column block, register) of lane
+// `lane` of a wave that computes the whole tile lies in the tile; part_of: 1 =
+// the imaginary part of a complex element.
+template <class Cfg>
+__device__ __forceinline__ void lp2_place(int q, int lane, int &row, int &col, int &part_of) {
+    constexpr int NACC = sizeof(typename Cfg::Acc) / (Cfg::F64 ? 8 : 4);
+    const int l32 = lane & 31, g = lane >> 5, l16 = lane & 15, g4 = lane >> 4;
+    const int rb = q / (Cfg::CBA * NACC), ca = q / NACC % Cfg::CBA, r = q % NACC;
+    part_of = 0;
+    if constexpr (Cfg::F64) {
+        row = rb * 16 + g4 + 4 * r;
+        col = Cfg::CB == 1 ? l16 : 32 * (ca / 2) + 2 * l16 + ca % 2;
+    } else if constexpr (Cfg::M16) {
+        row = rb * 16 + 4 * g4 + r;
+        col = ca * 16 + l16;
+    } else {
+        row = rb * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
+        if constexpr (Cfg::C32) {
+            col = Cfg::CB * l32 + ca / 2;
+            part_of = ca % 2;
+        } else {
+            col = Cfg::F32 ? Cfg::CB * l32 + ca : ca * 32 + l32;
+        }
+    }
+}
+
+// The tile whose k ranges are dealt over the workgroup's WK waves (a split
+// factor up to WK): each wave accumulates one range, the partial sums are
+// exchanged through LDS and added by accumulator register (wave w adds
+// registers w, w + WK, ...) in ascending range, then scaled and stored: the
+// sum and the rounding of the split-K slabs' reduction.  A factor above WK
+// has ranges on ceil(factor / WK) workgroups, whose waves write their slabs.
+template <class Cfg>
+__device__ __forceinline__ void lp2_tile_wk(const TileProblem &P, int tm, int tn, int part, uint8_t *lds) {
+    typedef typename std::conditional<Cfg::F64, double, float>::type E;
+    constexpr int NACC = sizeof(typename Cfg::Acc) / sizeof(E);
+    constexpr int NREG = Cfg::RB * Cfg::CBA * NACC;          // accumulator registers of a wave
+    constexpr int PER = (NREG + Cfg::WK - 1) / Cfg::WK;      // registers a wave adds
+    static_assert(NREG * 64 * (int)sizeof(E) <= Cfg::RING, "a wave's partial sums fit its ring");
+    const int m0 = tm * Cfg::BM;
+    const int n0 = Cfg::REG ? max(0, min(tn * Cfg::BN, P.n - Cfg::BN)) : tn * Cfg::BN;
+    const int lane = threadIdx.x & 63;
+    const int kw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr int WSTRIDE = Cfg::RING / (int)sizeof(E);      // a wave's partial sums start at its ring
+    // (a range past the last is empty; its zeros are not used)
+    lp2_tile<Cfg>(P, tm, tn, part * Cfg::WK + kw, lds + kw * Cfg::RING);
+    if (!Cfg::F64 && !Cfg::C32 && P.splits > Cfg::WK) {
+        const int range = part * Cfg::WK + kw;
+        if (range >= P.splits) return;
+        float *C = P.C + (int64_t)range * P.split_stride;
+        const float *mine = reinterpret_cast<const float *>(lds + kw * Cfg::RING) + lane;
+#pragma unroll
+        for (int q = 0; q < NREG; ++q) {
+            int row, col, part_of;
+            lp2_place<Cfg>(q, lane, row, col, part_of);
+            row += m0;
+            col += n0;
+            if (row < P.m && col < P.n && (!Cfg::REG || col >= tn * Cfg::BN)) C[(int64_t)row * P.n + col] = mine[q * 64];
+        }
+        return;
+    }
+    __syncthreads();
+    const E *sums = reinterpret_cast<const E *>(lds) + lane;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int q = kw + i * Cfg::WK;
+        if (NREG % Cfg::WK != 0 && q >= NREG) break;
+        E v = sums[q * 64];
+        for (int p = 1; p < P.splits; ++p) v += sums[p * WSTRIDE + q * 64];
+        int row, col, part_of;
+        lp2_place<Cfg>(q, lane, row, col, part_of);
+        row += m0;
+        col += n0;
+        if (row < P.m && col < P.n && (!Cfg::REG || col >= tn * Cfg::BN)) {
+            if constexpr (Cfg::F64) reinterpret_cast<double *>(P.C)[(int64_t)row * P.ldc + col] = v;
+            else if constexpr (Cfg::C32) P.C[2 * ((int64_t)row * P.ldc + col) + part_of] = v;
+            else P.C[(int64_t)row * P.ldc + col] = v * P.scale;
+        }
+    }
+}
+
+template <int MODE, int BM, int BN, int STAGES, int WM, int WN, int AROWB, int LDB, int MB, int WK>
+__device__ __forceinline__ void Lp2Cfg<MODE, BM, BN, STAGES, WM, WN, AROWB, LDB, MB, WK>::run(const TileProblem &P,
+                                                                                        int tm, int tn, int split,
+                                                                                        uint8_t *lds) {
+    typedef Lp2Cfg<MODE, BM, BN, STAGES, WM, WN, AROWB, LDB, MB, WK> Cfg;
+    if constexpr (WK) lp2_tile_wk<Cfg>(P, tm, tn, split, lds);
+    else lp2_tile<Cfg>(P, tm, tn, split, lds);
 }

@@ -390,3 +390,42 @@ def test_add_paper_size(dtype):
     B = synth.draw(g, (4096, 4096)) if dtype == "f32" else synth.draw64(g, (4096, 4096))
     C = host(mg.add(dev(A), dev(B), subtract=True))
     assert np.array_equal(C, oracle.add(A, B, subtract=True).astype(A.dtype))
+
+
+# The shapes where the choice of tile turns: fewer k-tiles of 16 than the four
+# or eight waves that share out k, one column and one row more than a tile of
+# 16, 32 or 64, whole and broken 16-byte chunks, a long k on few tiles
+CHOICE_SHAPES = [(1, 1, 1), (16, 16, 16), (17, 15, 33), (31, 2, 18), (32, 34, 130), (33, 33, 127), (64, 64, 1000),
+                 (65, 66, 2050), (107, 64, 1344), (100, 515, 77), (515, 100, 78), (260, 1030, 40), (1030, 262, 514)]
+
+
+@pytest.mark.parametrize("m,n,k", CHOICE_SHAPES)
+@pytest.mark.parametrize("kind", ["f64", "c32"])
+def test_chosen_tile_bound_and_strides(kind, m, n, k):
+    """The product without an explicit configuration: within the bound of the
+    oracle, nothing written outside C, and the same bits for contiguous
+    operands and for odd strides on bases off 16-byte alignment."""
+    log(f"{kind} chosen tile {(m, n, k)}")
+    if kind == "f64":
+        A, B = synth.pair64(m, n, k, seed=m + n + k)
+        R, run = oracle.gemm_dot2(A, B), mg.gemm_f64
+    else:
+        A, B = synth.pair_c64(m, n, k, seed=m + n + k)
+        R, run = oracle.gemm_c128(A, B), mg.gemm_c32
+    dA, dB = dev(A), dev(B)
+    C = host(run(dA, dB))
+    if kind == "f64":
+        _assert_f64(C, R, A, B, k, f"f64 chosen {(m, n, k)}")
+    else:
+        _assert_c32(C, R, A, B, k, f"c32 chosen {(m, n, k)}")
+    bufA = torch.full((m, k + 2 - k % 2 + 1), float("nan"), dtype=dA.dtype, device="cuda")
+    bufB = torch.full((k + 1, n + 2 - n % 2 + 1), float("nan"), dtype=dB.dtype, device="cuda")
+    bufA[:, 1:k + 1] = dA
+    bufB[:k, 1:n + 1] = dB
+    big = torch.full((m + 2, n + 3), float("nan"), dtype=dA.dtype, device="cuda")
+    run(bufA[:, 1:k + 1], bufB[:k, 1:n + 1], out=big[1:m + 1, 1:n + 1])
+    h = host(big)
+    assert np.array_equal(h[1:m + 1, 1:n + 1], C)
+    mask = np.ones(h.shape, dtype=bool)
+    mask[1:m + 1, 1:n + 1] = False
+    assert np.isnan(h[mask]).all()
