@@ -54,6 +54,7 @@ template <int BM, int BN, int WM, int WN, int BK>
 struct GsOps<F32Cfg<BM, BN, WM, WN, BK>> {
     typedef F32Cfg<BM, BN, WM, WN, BK> Cfg;
     static constexpr int ESZ = 4;
+    static constexpr bool NATURAL = false;
     static constexpr int NA = Cfg::AV, NB = Cfg::BV;
     typedef f32x16 Acc[Cfg::RB][Cfg::CB];
     // A vector q: tile row r, k offset c; B vector q: k offset kr, tile column c
@@ -84,6 +85,7 @@ template <int MODE, int BM, int BN, int BK>
 struct GsOps<LpCfg<MODE, BM, BN, BK>> {
     typedef LpCfg<MODE, BM, BN, BK> Cfg;
     static constexpr int ESZ = Cfg::T::IN_ESZ;
+    static constexpr bool NATURAL = Cfg::ROW_B;              // lane l%32 of block cb: column 32 cb + l%32
     static constexpr int NA = Cfg::AV, NB = Cfg::TKB;
     typedef f32x16 Acc[Cfg::RB][Cfg::CB];
     __device__ static __forceinline__ void a_pos(int q, int &r, int &c) {
@@ -92,9 +94,7 @@ struct GsOps<LpCfg<MODE, BM, BN, BK>> {
         c = (idx % Cfg::VPR) * (16 / ESZ);
     }
     __device__ static __forceinline__ void b_pos(int q, int &kr, int &c) {
-        const int kb = threadIdx.x % Cfg::KBLK, nb = threadIdx.x / Cfg::KBLK;
-        kr = kb * Cfg::TKB + q;
-        c = nb * Cfg::VN;
+        Cfg::b_pos(q, kr, c);
     }
     __device__ static __forceinline__ void store(uint8_t *stage, const u32x4 *v) {
         LpStage<Cfg> R;
@@ -169,7 +169,8 @@ __device__ __forceinline__ u32x4 gs_ld16_masked(gs_gu8 *base, int64_t ld, int r,
 
 // The accumulators of one tile to C (the element mapping of tile_epilogue:
 // lane l%32 of block cb holds output column CB*(l%32) + cb of the wave's
-// columns; register r of the 32x32 block holds row 8(r/4) + 4(l/32) + r%4).
+// columns, or, with row-major B in LDS, 32*cb + l%32; register r of the 32x32
+// block holds row 8(r/4) + 4(l/32) + r%4).
 // Each lane's row pointer is computed once; the rows it stores are a fixed
 // offset times ldc from it (scalar arithmetic).  An interior tile stores
 // without any bound test.
@@ -180,7 +181,9 @@ __device__ __forceinline__ void gs_epilogue(gs_gf32 *C, int64_t ldc, int M, int 
     const int wave = threadIdx.x >> 6;
     const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
     const int l32 = lane & 31, g = lane >> 5;
-    const int col = n0 + wn * Cfg::TN + Cfg::CB * l32;
+    constexpr bool NAT = GsOps<Cfg>::NATURAL;
+    constexpr int CS = NAT ? 32 : 1;                         // columns between a lane's blocks
+    const int col = n0 + wn * Cfg::TN + (NAT ? l32 : Cfg::CB * l32);
     const int row0 = m0 + wm * Cfg::TM + 4 * g;
     gs_gf32 *base = C + (int64_t)row0 * ldc + col;
     if (m0 + Cfg::BM <= M && n0 + Cfg::BN <= N) {
@@ -190,12 +193,12 @@ __device__ __forceinline__ void gs_epilogue(gs_gf32 *C, int64_t ldc, int M, int 
             for (int r = 0; r < 16; ++r) {
                 gs_gf32 *p = base + (int64_t)(rb * 32 + 8 * (r >> 2) + (r & 3)) * ldc;
 #pragma unroll
-                for (int cb = 0; cb < Cfg::CB; ++cb) p[cb] = acc[rb][cb][r] * scale;
+                for (int cb = 0; cb < Cfg::CB; ++cb) p[CS * cb] = acc[rb][cb][r] * scale;
             }
         return;
     }
     const int rows_left = M - row0;
-    const bool full_cols = col + Cfg::CB <= N;
+    const bool full_cols = col + CS * (Cfg::CB - 1) < N;
 #pragma unroll
     for (int rb = 0; rb < Cfg::RB; ++rb) {
 #pragma unroll
@@ -205,11 +208,11 @@ __device__ __forceinline__ void gs_epilogue(gs_gf32 *C, int64_t ldc, int M, int 
             gs_gf32 *p = base + (int64_t)d * ldc;
             if (full_cols) {
 #pragma unroll
-                for (int cb = 0; cb < Cfg::CB; ++cb) p[cb] = acc[rb][cb][r] * scale;
+                for (int cb = 0; cb < Cfg::CB; ++cb) p[CS * cb] = acc[rb][cb][r] * scale;
             } else {
 #pragma unroll
                 for (int cb = 0; cb < Cfg::CB; ++cb)
-                    if (col + cb < N) p[cb] = acc[rb][cb][r] * scale;
+                    if (col + CS * cb < N) p[CS * cb] = acc[rb][cb][r] * scale;
             }
         }
     }
@@ -508,9 +511,12 @@ __device__ __forceinline__ bool gs_step(const GroupDesc *__restrict__ descs, con
     }
     // keep this step's set (staged one step ago, reloaded by the next step)
     // live until the reload, so that its registers are not lent to
-    // temporaries, which would have to wait for its load
+    // temporaries, which would have to wait for its load (not where the
+    // registers do not suffice: the 8-bit tiles' wider fragments, three sets)
+    if constexpr (R::ESZ != 1 && DEPTH != 3) {
 #pragma unroll
-    for (int q = 0; q < R::NV; ++q) asm volatile("" ::"v"(ring[U % DEPTH][q]));
+        for (int q = 0; q < R::NV; ++q) asm volatile("" ::"v"(ring[U % DEPTH][q]));
+    }
     __syncthreads();
     ++s.step;
     s.ci = ni;

@@ -14,20 +14,91 @@
 // one A row (lane l: row l%32) and of one B column (lane l: column l%32); the
 // two lane halves (l/32) hold two disjoint k-groups, A and B alike.  A is
 // row-major (k contiguous) in HBM, so an A row is staged as is.  B is
-// row-major k x n (n contiguous), so the staging transposes it in registers:
-// each thread loads TKB rows of 16 bytes (VN columns) and writes VN LDS rows
-// of TKB consecutive-k elements ("B^T" rows).  Lanes of one LDS write cover
-// one B^T row, so those writes are free of bank conflicts, and the global
-// loads of a wave cover whole row segments of B.
+// row-major k x n (n contiguous):
+//   * BF16, F16, FP8: its rows are staged as they are too, and each lane's
+//     consecutive k are gathered by the transposing LDS reads.  Consecutive
+//     lanes load consecutive 16-byte chunks of a row, so one load instruction
+//     touches a few rows.  (Transposing in registers at staging, as below, had
+//     every lane of a load on another row, one address cycle and one cache
+//     line each, and the address units bound the kernels: 512 grouped bfloat16
+//     problems 145 us against 131 now, 48 grouped E4M3 problems of 64..4096
+//     156 against 112, binary16 2047 x 1999 x 2501 112 against 105.)
+//   * split-BF16x3: the staging transposes it in registers while it splits:
+//     each thread loads TKB rows of 16 bytes (VN columns) and writes VN LDS
+//     rows of TKB consecutive-k elements ("B^T" rows); lanes of one LDS write
+//     cover one B^T row, so those writes are free of bank conflicts.
 //
-// Column permutation: as in the FP32 tile, lane jj of accumulator block cb
-// computes output column CB*jj + cb of the wave's columns, so the epilogue
-// stores CB consecutive floats per lane.  The B^T row of wave-local column
-// n = CB*jj + cb is stored at LDS row 32*cb + jj, which makes every fragment
-// read a run of consecutive LDS rows (conflict-free with the padded stride).
+// Column permutation (split-BF16x3): as in the FP32 tile, lane jj of
+// accumulator block cb computes output column CB*jj + cb of the wave's columns,
+// so the epilogue stores CB consecutive floats per lane.  The B^T row of
+// wave-local column n = CB*jj + cb is stored at LDS row 32*cb + jj, which makes
+// every fragment read a run of consecutive LDS rows (conflict-free with the
+// padded stride).  The other forms' columns are in natural order.
 #pragma once
 
 #include "tile_common.hpp"
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+
+// The MFMA B operand (consecutive k of one column per lane) of the 32 columns
+// from n0 and the k-step from k0, gathered from row-major LDS rows of `rowb`
+// bytes with the transposing reads (see tile_lp2.hpp for their lane layout);
+// `swz` gives the chunk swizzle of a row.  16-bit: 16 k, 8-bit: 64 k.
+template <class Swz>
+__device__ __forceinline__ u32x4 lp_b_fragment16(const uint8_t *Bs, int rowb, int k0, int n0, Swz swz) {
+    const int lane = threadIdx.x & 63;
+    const int p16 = lane & 15, G = lane >> 4;
+    const int n = n0 + 16 * (G & 1) + 4 * (p16 & 3);
+    s16x4 hv[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int k = k0 + 8 * (G >> 1) + 4 * h + (p16 >> 2);
+        const uint8_t *a = Bs + k * rowb + 16 * ((n >> 3) ^ swz(k)) + 2 * (n & 7);
+        hv[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)a);
+    }
+    const i32x2 lo = __builtin_bit_cast(i32x2, hv[0]);
+    const i32x2 hi = __builtin_bit_cast(i32x2, hv[1]);
+    return (u32x4){(uint32_t)lo[0], (uint32_t)lo[1], (uint32_t)hi[0], (uint32_t)hi[1]};
+}
+
+template <class Swz>
+__device__ __forceinline__ i32x8 lp_b_fragment8(const uint8_t *Bs, int rowb, int k0, int n0, Swz swz) {
+    const int lane = threadIdx.x & 63;
+    const int p16 = lane & 15, G = lane >> 4;
+    // (the swizzle repeats every 8 rows: one address, the four reads 8 rows apart)
+    const int k = k0 + 32 * (G >> 1) + (p16 >> 1);
+    const uint8_t *a = Bs + k * rowb + 16 * (((n0 >> 4) + (G & 1)) ^ swz(p16 >> 1)) + 8 * (p16 & 1);
+    i32x2 q[4];
+#pragma unroll
+    for (int h = 0; h < 4; ++h)
+        q[h] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) i32x2 *)(a + 8 * h * rowb));
+    return (i32x8){q[0][0], q[0][1], q[1][0], q[1][1], q[2][0], q[2][1], q[3][0], q[3][1]};
+}
+
+// Natural-column epilogue: lane l%32 of accumulator block cb holds output
+// column 32*cb + l%32 of the wave's columns.
+template <class Cfg>
+__device__ __forceinline__ void lp2_epilogue(float *__restrict__ C, int64_t ldc, int M, int N, int m0, int n0,
+                                             float scale, const f32x16 (&acc)[Cfg::RB][Cfg::CB]) {
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
+    const int l32 = lane & 31, g = lane >> 5;
+#pragma unroll
+    for (int rb = 0; rb < Cfg::RB; ++rb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int row = m0 + wm * Cfg::TM + rb * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
+            if (row >= M) continue;
+            float *p = C + (int64_t)row * ldc;
+#pragma unroll
+            for (int cb = 0; cb < Cfg::CB; ++cb) {
+                const int col = n0 + wn * Cfg::TN + cb * 32 + l32;
+                if (col < N) p[col] = acc[rb][cb][r] * scale;
+            }
+        }
+}
 
 template <int MODE> struct LpTraits;
 template <> struct LpTraits<GEMM_MODE_BF16> {
@@ -69,7 +140,13 @@ struct LpCfg {
         if constexpr (ROW / 16 == 8) return (r >> 1) & 7;
         return ((r >> 1) ^ (r >> 2)) & 3;
     }
-    static constexpr int PLANE_A = BM * RSA, PLANE_B = BN * RS;
+    // row-major B in LDS, its 16-byte chunks XOR-swizzled by row
+    static constexpr bool ROW_B = T::PLANES == 1;
+    static constexpr int B_ROWB = BN * T::IN_ESZ, B_CPR = B_ROWB / 16;
+    __device__ static __forceinline__ int b_swz(int k) {
+        return (T::IN_ESZ == 2 ? 4 * (k & 3) : 2 * (k & 7)) & (B_CPR - 1);
+    }
+    static constexpr int PLANE_A = BM * RSA, PLANE_B = ROW_B ? BK * B_ROWB : BN * RS;
     static constexpr int A_BYTES = T::PLANES * PLANE_A, B_BYTES = T::PLANES * PLANE_B;
     static constexpr int STAGE = A_BYTES + B_BYTES;
     static constexpr int LDS_BYTES = 2 * STAGE;
@@ -80,6 +157,17 @@ struct LpCfg {
     static constexpr int TKB = BK * NBLK / GEMM_THREADS;   // k rows per thread's B block
     static constexpr int KBLK = BK / TKB;                  // k blocks per k-tile
     static constexpr int MFMA_K = T::KCH;
+    // B vector q of this thread: k row kr of the k-tile, column c
+    __device__ static __forceinline__ void b_pos(int q, int &kr, int &c) {
+        if constexpr (ROW_B) {
+            const int idx = threadIdx.x + q * GEMM_THREADS;
+            kr = idx / NBLK;
+            c = (idx % NBLK) * VN;
+        } else {
+            kr = (threadIdx.x % KBLK) * TKB + q;
+            c = (threadIdx.x / KBLK) * VN;
+        }
+    }
     static_assert((RS / 16) % 2 == 1, "row stride must be an odd multiple of 16 bytes");
     static_assert(RB >= 1 && (CB == 1 || CB == 2 || CB == 4), "wave tile");
     static_assert(AV >= 1 && AV * GEMM_THREADS == BM * VPR, "A staging");
@@ -156,10 +244,12 @@ __device__ __forceinline__ void lp_load_tiles(const TileProblem &P, int m0, int 
         const int c = (idx % Cfg::VPR) * (16 / ESZ);
         R.a[q] = lp_load16<ESZ>(A, P.lda, m0 + r, k0 + c, P.m, P.k);
     }
-    const int kb = tid % Cfg::KBLK, nb = tid / Cfg::KBLK;
 #pragma unroll
-    for (int e = 0; e < Cfg::TKB; ++e)
-        R.b[e] = lp_load16<ESZ>(B, P.ldb, k0 + kb * Cfg::TKB + e, n0 + nb * Cfg::VN, P.k, P.n);
+    for (int e = 0; e < Cfg::TKB; ++e) {
+        int kr, c;
+        Cfg::b_pos(e, kr, c);
+        R.b[e] = lp_load16<ESZ>(B, P.ldb, k0 + kr, n0 + c, P.k, P.n);
+    }
 }
 
 // Element c (of width W bits) of a 16-byte row vector.
@@ -194,6 +284,16 @@ __device__ __forceinline__ void lp_store_tiles(uint8_t *stage, const LpStage<Cfg
         } else {
             *reinterpret_cast<u32x4 *>(As + r * Cfg::RSA + v * 16) = R.a[q];
         }
+    }
+    if constexpr (Cfg::ROW_B) {
+        // ---- B: row chunks as they are
+#pragma unroll
+        for (int q = 0; q < Cfg::TKB; ++q) {
+            int kr, c;
+            Cfg::b_pos(q, kr, c);
+            *reinterpret_cast<u32x4 *>(Bs + kr * Cfg::B_ROWB + 16 * ((c / Cfg::VN) ^ Cfg::b_swz(kr))) = R.b[q];
+        }
+        return;
     }
     // ---- B: transpose the thread's TKB x VN block into VN B^T rows
     const int kb = tid % Cfg::KBLK, nb = tid / Cfg::KBLK;
@@ -243,7 +343,7 @@ __device__ __forceinline__ void lp_compute_stage(const uint8_t *stage, f32x16 (&
 #pragma unroll
     for (int kc = 0; kc < Cfg::ROW / CHUNK_BYTES; ++kc) {
         if constexpr (MODE == GEMM_MODE_F8E4M3) {
-            i32x8 af[Cfg::RB], bf[Cfg::CB];
+            i32x8 af[Cfg::RB];
 #pragma unroll
             for (int rb = 0; rb < Cfg::RB; ++rb) {
                 // the lane's two chunks: 4 kc + 2 g and the next
@@ -256,20 +356,16 @@ __device__ __forceinline__ void lp_compute_stage(const uint8_t *stage, f32x16 (&
                 af[rb] = (i32x8){(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3],
                                  (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
             }
+            // (one B fragment at a time: the grouped kernel's registers)
 #pragma unroll
             for (int cb = 0; cb < Cfg::CB; ++cb) {
-                const uint8_t *p = Bs + cb * 32 * Cfg::RS + kc * CHUNK_BYTES;
-                const u32x4 lo = *reinterpret_cast<const u32x4 *>(p);
-                const u32x4 hi = *reinterpret_cast<const u32x4 *>(p + 16);
-                bf[cb] = (i32x8){(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3],
-                                 (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+                const i32x8 bf = lp_b_fragment8(stage + Cfg::A_BYTES, Cfg::B_ROWB, 64 * kc, wn * Cfg::TN + cb * 32,
+                                                [](int k) { return Cfg::b_swz(k); });
+#pragma unroll
+                for (int rb = 0; rb < Cfg::RB; ++rb)
+                    acc[rb][cb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[rb], bf, acc[rb][cb], 0, 0, 0, 0,
+                                                                                 0, 0);
             }
-#pragma unroll
-            for (int rb = 0; rb < Cfg::RB; ++rb)
-#pragma unroll
-                for (int cb = 0; cb < Cfg::CB; ++cb)
-                    acc[rb][cb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[rb], bf[cb], acc[rb][cb], 0,
-                                                                                 0, 0, 0, 0, 0);
         } else {
             u32x4 af[Cfg::RB], bf[Cfg::CB];
 #pragma unroll
@@ -278,8 +374,13 @@ __device__ __forceinline__ void lp_compute_stage(const uint8_t *stage, f32x16 (&
                     As + rb * 32 * Cfg::RSA +
                     (Cfg::SWZ_A ? 16 * ((2 * kc + g) ^ Cfg::a_swz(ar)) : kc * CHUNK_BYTES));
 #pragma unroll
-            for (int cb = 0; cb < Cfg::CB; ++cb)
-                bf[cb] = *reinterpret_cast<const u32x4 *>(Bs + cb * 32 * Cfg::RS + kc * CHUNK_BYTES);
+            for (int cb = 0; cb < Cfg::CB; ++cb) {
+                if constexpr (Cfg::ROW_B)
+                    bf[cb] = lp_b_fragment16(stage + Cfg::A_BYTES, Cfg::B_ROWB, 16 * kc, wn * Cfg::TN + cb * 32,
+                                             [](int k) { return Cfg::b_swz(k); });
+                else
+                    bf[cb] = *reinterpret_cast<const u32x4 *>(Bs + cb * 32 * Cfg::RS + kc * CHUNK_BYTES);
+            }
             if constexpr (MODE == GEMM_MODE_F32_SPLIT_BF16X3) {
                 u32x4 al[Cfg::RB], bl[Cfg::CB];
 #pragma unroll
@@ -359,7 +460,8 @@ __device__ __forceinline__ void lp_tile(const TileProblem &P, int tm, int tn, in
     int64_t ldc;
     float scale;
     epilogue_target(P, split, C, ldc, scale);
-    tile_epilogue<Cfg>(C, ldc, P.m, P.n, m0, n0, scale, acc);
+    if constexpr (Cfg::ROW_B) lp2_epilogue<Cfg>(C, ldc, P.m, P.n, m0, n0, scale, acc);
+    else tile_epilogue<Cfg>(C, ldc, P.m, P.n, m0, n0, scale, acc);
 }
 
 template <int MODE, int BM, int BN, int BK>

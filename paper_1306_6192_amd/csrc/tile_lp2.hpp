@@ -54,9 +54,7 @@
 #include "tile_c32.hpp"
 #include "tile_common.hpp"
 #include "tile_f64.hpp"
-
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef int i32x2 __attribute__((ext_vector_type(2)));
+#include "tile_lp.hpp"
 
 // A 16-byte chunk of zeros in device memory: the source of k positions past
 // the end of the matrices.
@@ -575,30 +573,6 @@ __device__ __forceinline__ void lp2_epilogue16(float *__restrict__ C, int64_t ld
             for (int cb = 0; cb < Cfg::CB; ++cb) {
                 const int col = n0 + wn * Cfg::TN + cb * 16 + p16;
                 if (col < N) p[col] = acc[rb][cb][i] * scale;
-            }
-        }
-}
-
-// Natural-column epilogue: lane l%32 of accumulator block cb holds output
-// column 32*cb + l%32 of the wave's columns.
-template <class Cfg>
-__device__ __forceinline__ void lp2_epilogue(float *__restrict__ C, int64_t ldc, int M, int N, int m0, int n0,
-                                             float scale, const f32x16 (&acc)[Cfg::RB][Cfg::CB]) {
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
-    const int l32 = lane & 31, g = lane >> 5;
-#pragma unroll
-    for (int rb = 0; rb < Cfg::RB; ++rb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = m0 + wm * Cfg::TM + rb * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-            if (row >= M) continue;
-            float *p = C + (int64_t)row * ldc;
-#pragma unroll
-            for (int cb = 0; cb < Cfg::CB; ++cb) {
-                const int col = n0 + wn * Cfg::TN + cb * 32 + l32;
-                if (col < N) p[col] = acc[rb][cb][r] * scale;
             }
         }
 }
