@@ -351,7 +351,7 @@ int upload_plan(const GroupPlan &plan, hipStream_t s, const void **dev_out) {
         st->bytes[b] = std::max<size_t>(bytes, 4096);
     }
     plan_image_write(plan, st->host[b]);
-    MG_HIP(hipMemcpyAsync(db->ptr, st->host[b], bytes, hipMemcpyHostToDevice, s));
+    MG_HIP(launch_upload(db->ptr, st->host[b], (int64_t)bytes, s));
     MG_HIP(hipEventRecord(st->ev[b], s));
     *dev_out = db->ptr;
     return GEMM_OK;

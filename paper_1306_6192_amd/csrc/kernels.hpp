@@ -91,5 +91,8 @@ hipError_t launch_zero_rows(void *C, int64_t ld_bytes, int m, int64_t row_bytes,
 // to 16, the padding zero.
 hipError_t launch_presplit(const float *A, int64_t lda, const float *B, int64_t ldb, int m, int n, int k,
                            uint16_t *Ap, uint16_t *Bp, hipStream_t s);
+// `bytes` (a multiple of 16) from pinned host memory to device memory, both
+// 16-byte aligned (misc.hip).
+hipError_t launch_upload(void *dst, const void *pinned, int64_t bytes, hipStream_t s);
 hipError_t launch_errnorm(const float *C, int64_t ldc, const double *R, int64_t ldr, int64_t m,
                           int64_t n, double *out3, double *partials, int nparts, hipStream_t s);

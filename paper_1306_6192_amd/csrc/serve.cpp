@@ -243,7 +243,7 @@ int Server::launch_batch(Slot &s, std::vector<Request *> &b) {
         }
         // the slot is idle: its previous upload has completed
         plan_image_write(plan, s.host);
-        MG_HIP(hipMemcpyAsync(s.descs.ptr, s.host, bytes, hipMemcpyHostToDevice, s.stream));
+        MG_HIP(launch_upload(s.descs.ptr, s.host, (int64_t)bytes, s.stream));
         rc = enqueue_group(plan, s.descs.ptr, s.stream);
         if (rc != GEMM_OK) return rc;
     }
