@@ -48,9 +48,8 @@ const KernelCfg *lp_configs_split(int *count) {
 const GroupedKernel *lp_grouped_split(int variant) {
     static const GroupedKernel k[2] = {
         [] {
-            GroupedKernel g = make_grouped<LpCfg<GEMM_MODE_F32_SPLIT_BF16X3, 128, 128, 16>,
-                                           LpCfg<GEMM_MODE_F32_SPLIT_BF16X3, 128, 128, 16>, GROUPED_ONE_OCC,
-                                           GROUPED_ONE_DEPTH>(0, 0, 0, 5);
+            GroupedKernel g =
+                make_grouped_one<LpCfg<GEMM_MODE_F32_SPLIT_BF16X3, 128, 128, 16>>(0, 0, 5, GROUPED_DEEP_16);
             int n = 0;
             lp_configs_split(&n);
             g.cfg_idx[0] = g.cfg_idx[1] = g.alone_idx[0] = n - 1;

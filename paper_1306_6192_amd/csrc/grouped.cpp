@@ -274,6 +274,7 @@ int build_group_plan(const gemm_problem_t *ps, int32_t count, GroupPlan &plan, i
     }
     plan.total_tiles = (int)total;
     plan.nwg = (int)std::min<int64_t>(total, slots);
+    plan.deep = plan.gk->launch_deep && (double)total < plan.gk->deep_below * (double)slots;
     if (total > 0) build_schedule(plan, cost, ntiles);
     return GEMM_OK;
 }
@@ -305,7 +306,7 @@ int enqueue_group(const GroupPlan &plan, const void *dev_image, hipStream_t s) {
     G.wg_first = reinterpret_cast<const int32_t *>(d);
     d += align256(plan.wg_first.size() * sizeof(int32_t));
     G.tiles = reinterpret_cast<const GroupTile *>(d);
-    MG_HIP(plan.gk->launch(G, plan.nwg, s));
+    MG_HIP((plan.deep ? plan.gk->launch_deep : plan.gk->launch)(G, plan.nwg, s));
     return GEMM_OK;
 }
 

@@ -60,6 +60,10 @@ struct GroupedKernel {
     int wg_per_cu;             // resident workgroups per CU (launch bound and LDS)
     int lds_bytes;             // LDS per workgroup
     GroupedLaunchFn launch;
+    // The same tiles with one more k-tile in flight, for launches of fewer
+    // than `deep_below` output tiles per resident workgroup (0: never).
+    GroupedLaunchFn launch_deep;
+    double deep_below;
 };
 
 // Tables of the configurations compiled for each mode (defined in the

@@ -30,7 +30,15 @@ template <int A, int B> struct cmax { static constexpr int v = A > B ? A : B; };
 // On the 512-problem workload variant 0 measured faster: the stream is bound
 // by its per-step instructions, which more resident waves overlap, and the
 // second tile's registers or a deeper ring do not fit three workgroups.
+// Variant 0 keeps one k-tile in flight per workgroup where the workgroups have
+// several output tiles each (512 problems of 32..1024 in bfloat16: 127 us
+// against 137 with two), and two where a launch has about as many tiles as
+// resident workgroups and ends with its longest k loop, whose loads nothing
+// else covers: 40 problems 36 -> 30 us, 151 (1.3 tiles per workgroup) 42 -> 38,
+// 200 (1.6) 48 -> 43, level at 2.5; split-BF16x3 40 problems 72 -> 59; E4M3
+// 25.6 -> 22.3, level at 1.6.  FP32, bound by its matrix pipe, gains nothing.
 constexpr int GROUPED_ONE_OCC = 3, GROUPED_ONE_DEPTH = 2;
+constexpr double GROUPED_DEEP_16 = 2.0, GROUPED_DEEP_8 = 1.5;
 constexpr int GROUPED_TWO_OCC = 2, GROUPED_TWO_DEPTH = 4;
 
 template <class Cfg, int OCC>
@@ -58,7 +66,18 @@ constexpr GroupedKernel make_grouped(int cfg0, int cfg1, int alone0, int alone1)
                              ? (160 * 1024 / (2 * GsRing<Cfg0, Cfg1>::STAGE))
                              : OCC,
                          2 * GsRing<Cfg0, Cfg1>::STAGE,
-                         launch_grouped_t<Cfg0, Cfg1, OCC, DEPTH>};
+                         launch_grouped_t<Cfg0, Cfg1, OCC, DEPTH>,
+                         nullptr,
+                         0.0};
+}
+
+// A one-tile grouped kernel with its deeper form (see GROUPED_ONE_DEPTH).
+template <class Cfg>
+constexpr GroupedKernel make_grouped_one(int cfg, int alone0, int alone1, double deep_below) {
+    GroupedKernel g = make_grouped<Cfg, Cfg, GROUPED_ONE_OCC, GROUPED_ONE_DEPTH>(cfg, cfg, alone0, alone1);
+    g.launch_deep = launch_grouped_t<Cfg, Cfg, GROUPED_ONE_OCC, GROUPED_ONE_DEPTH + 1>;
+    g.deep_below = deep_below;
+    return g;
 }
 
 template <class Cfg, int OCC, int CHUNK = 0, int PRESPLIT = 0>

@@ -222,3 +222,31 @@ def test_tune_grouped_mix_records_a_variant(tmp_path):
                                "paper_1306_6192_amd", "tuning", "mi355x.jsonl")
         if os.path.exists(shipped):
             _lib.check(lib.gemm_tuner_load(shipped.encode()))
+
+
+# 768 workgroups are resident: lists of one tile per problem just below and at
+# the 2 (E4M3: 1.5) tiles per workgroup from which the launch keeps one k-tile
+# in flight instead of two, and single-tile lists
+@pytest.mark.parametrize("count", [1, 2, 1151, 1152, 1535, 1536])
+@pytest.mark.parametrize("mode", [mg.MODE_BF16, mg.MODE_F16, mg.MODE_F8E4M3, mg.MODE_SPLIT_BF16X3],
+                         ids=["bf16", "f16", "e4m3", "split_bf16x3"])
+def test_grouped_either_depth_equals_plain(mode, count):
+    """The launch's two forms give the plain launch's bits: k below one
+    k-tile, one more than it, several; odd strides."""
+    log(f"grouped depth {mode} {count}")
+    g = torch.Generator(device="cuda").manual_seed(count)
+    ks = [1, 7, 33, 65, 129, 200, 300, 514]
+    m, n = 31, 37
+    A = torch.rand((m, 520), device="cuda", generator=g) * 2 - 1
+    B = torch.rand((520, n + 2), device="cuda", generator=g) * 2 - 1
+    if mode in (mg.MODE_BF16, mg.MODE_F16):
+        A, B = mg.convert(A, mode), mg.convert(B, mode)
+    elif mode == mg.MODE_F8E4M3:
+        A, B = mg.quantize_e4m3(A)[0], mg.quantize_e4m3(B)[0]
+    views = [(A[:, i % 3:i % 3 + k], B[:k, i % 2:i % 2 + n]) for i, k in enumerate(ks)]
+    out = torch.full((count, m, n), float("nan"), device="cuda")
+    mg.grouped([(*views[i % len(ks)], out[i]) for i in range(count)], mode=mode)
+    got = host(out).view(np.uint32)
+    for i, (a, b) in enumerate(views[:count]):
+        want = host(mg.gemm(a, b, mode=mode, cfg=0, split_k=1)).view(np.uint32)
+        assert (got[i::len(ks)] == want).all(), ks[i]
