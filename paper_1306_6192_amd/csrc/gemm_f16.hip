@@ -30,6 +30,15 @@ static const KernelCfg kTable[] = {
     make_cfg<Lp2Cfg<GEMM_MODE_F16, 128, 256, 4, 2, 2, 0, 16, 16>, 1, 8>(),
     make_cfg<Lp2Cfg<GEMM_MODE_F16, 128, 128, 4, 2, 2, 0, 16, 16>, 2, 8>(),
     make_cfg<Lp2Cfg<GEMM_MODE_F16, 128, 128, 2, 2, 2, 128, 16, 16>, 2, 8>(),
+    // waves along k (each a tile of its own LDS ring and k range), for products
+    // whose larger tiles would leave CUs idle: 16-byte direct loads (k-tiles of
+    // 32, 64, 32), then (any shape) loads through registers
+    make_fused<Lp2Cfg<GEMM_MODE_F16, 32, 64, 2, 1, 1, 64, 16, 32, 8>, 2, 8>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F16, 32, 64, 2, 1, 1, 128, 16, 32, 4>, 2, 8>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F16, 64, 64, 2, 1, 1, 64, 16, 32, 8>, 2, 8>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F16, 32, 64, 2, 1, 1, 64, 0, 32, 4>, 2>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F16, 32, 64, 2, 1, 1, 64, 0, 32, 8>, 2>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F16, 64, 64, 2, 1, 1, 64, 0, 32, 8>, 2>(),
 };
 
 const KernelCfg *lp_configs_f16(int *count) {

@@ -51,6 +51,17 @@ static const KernelCfg kF32Configs[] = {
     // of 16, four waves: 128 x 128 and 64 x 64
     make_cfg<Lp2Cfg<GEMM_MODE_F32, 128, 128, 4, 2, 2, 64, 4>, 2>(),
     make_cfg<Lp2Cfg<GEMM_MODE_F32, 64, 64, 4, 2, 2, 64, 4>, 4>(),
+    // waves along k (each a tile of its own LDS ring and k range), for products
+    // whose larger tiles would leave CUs idle: 16-byte direct loads, then (any
+    // shape) loads through registers
+    make_fused<Lp2Cfg<GEMM_MODE_F32, 32, 32, 4, 1, 1, 64, 16, 32, 4>, 2, 4>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F32, 32, 32, 4, 1, 1, 64, 16, 32, 8>, 2, 4>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F32, 32, 64, 2, 1, 1, 64, 16, 32, 8>, 2, 4>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F32, 64, 64, 2, 1, 1, 64, 16, 32, 8>, 2, 4>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F32, 32, 32, 2, 1, 1, 64, 0, 32, 4>, 2>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F32, 32, 32, 2, 1, 1, 64, 0, 32, 8>, 2>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F32, 32, 64, 2, 1, 1, 64, 0, 32, 8>, 2>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F32, 64, 64, 2, 1, 1, 64, 0, 32, 8>, 2>(),
 };
 
 const KernelCfg *f32_configs(int *count) {

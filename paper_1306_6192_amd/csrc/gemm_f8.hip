@@ -17,6 +17,13 @@ static const KernelCfg kTable[] = {
     // register-staged 128 x 128 with k-tiles of 64 (half the LDS): the
     // grouped launch's large tile (16 KB of operands per k-tile)
     make_cfg<LpCfg<GEMM_MODE_F8E4M3, 128, 128, 64>, 3>(),
+    // waves along k (each a tile of its own LDS ring and k range), for products
+    // whose larger tiles would leave CUs idle: 16-byte direct loads, then (any
+    // shape) loads through registers
+    make_fused<Lp2Cfg<GEMM_MODE_F8E4M3, 32, 64, 2, 1, 1, 64, 16, 32, 8>, 2, 16>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F8E4M3, 64, 64, 2, 1, 1, 64, 16, 32, 8>, 2, 16>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F8E4M3, 32, 64, 2, 1, 1, 64, 0, 32, 4>, 2>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F8E4M3, 32, 64, 2, 1, 1, 64, 0, 32, 8>, 2>(),
 };
 
 const KernelCfg *lp_configs_f8(int *count) {

@@ -71,6 +71,8 @@ void heuristic_choose(int mode, int64_t m, int64_t n, int64_t k, int *cfg_out, i
         // chunked (asynchronous-copy) tiles need k and n in whole 16-byte
         // chunks; where they apply they sustain 1.4x (16-bit) to 3.5x (FP8),
         // and 1.1x (FP32) the register-staged tile's rate at 8192^3
+        // the tiles with waves along k are chosen by measurement only
+        if (kc.fused) continue;
         if (kc.chunk && (k % kc.chunk || n % kc.chunk)) continue;
         if (kc.presplit && !presplit_shape_ok(n, k)) continue;
         // the pre-split split-BF16x3 path runs at about 1.75x the register-
