@@ -65,9 +65,10 @@ typedef enum {
  *                    C = hiA hiB + hiA loB + loA hiB (compensated BF16),
  *                    the three products summed per 16 k in the order
  *                    loA hiB, hiA loB, hiA hiB.  The split happens at
- *                    tile staging, or (n a multiple of 8) once per operand
- *                    into a library workspace of 6*k16*(m + n) bytes,
- *                    k16 = k rounded up to 16; both give the same bits. */
+ *                    tile staging, or (n a multiple of 8, or m, n and k at
+ *                    least 512) once per operand into a library workspace of
+ *                    6*k16*(m + n8) bytes, k16 = k rounded up to 16 and n8 = n
+ *                    rounded up to 8; both give the same bits. */
 typedef enum {
     GEMM_MODE_F32 = 0,
     GEMM_MODE_BF16 = 1,
@@ -108,25 +109,35 @@ typedef struct gemm_problem {
  * partial sums go to a library-owned workspace and are summed in a fixed
  * order, so a given (mode, m, n, k) always produces the same bits.  The
  * workspace (one per device and stream, grown on demand, kept until the
- * process ends) also holds the split-BF16x3 operand copies. */
+ * process ends; at most 512 MB of it packed copies) also holds the
+ * split-BF16x3 operand copies and the packed copies of ragged operands (see
+ * gemm_plain_cfg).  Under stream capture a workspace that is too small is
+ * replaced, not freed: graphs captured before keep theirs. */
 int gemm_plain(const gemm_problem_t *p, void *stream);
 
 /* As gemm_plain with an explicit tile configuration (index into
  * gemm_config_info) and split-K factor (>= 1).  For tuning and tests.
  * Configurations whose k-tile is copied straight into LDS in 16-byte chunks
  * need k and n multiples of the chunk (16 bytes of elements), lda and ldb
- * likewise and 16-byte aligned A and B; for any other problem the
- * register-staged configuration of the same tile size runs instead.  Split-K
+ * likewise and 16-byte aligned A and B.  Any other problem runs them on
+ * packed copies of its operands, rows padded to whole chunks (m, n and k at
+ * least 512, FP32 m and n 2048, copies of at most 512 MB), or runs the
+ * register-staged configuration of the same tile size instead.
+ * Configurations whose waves share out k (4 or 8 waves; for them
+ * gemm_config_info's waves is the number of k ranges a workgroup takes) add a
+ * split factor of up to that in the workgroup, without slabs.  Split-K
  * cuts k into ranges of whole grains (32 k for FP32 and split-BF16x3, 64 for
  * BF16 and F16, 128 for FP8), each a whole number of every configuration's
  * k-tiles, so for a given split factor every configuration of a mode gives
  * the same bits. */
 int gemm_plain_cfg(const gemm_problem_t *p, int32_t cfg, int32_t split_k, void *stream);
 
-/* Device workspace bytes gemm_plain uses for this problem (split-K partial
- * slabs of split*m*n float32, plus the split-BF16x3 operand copies when the
- * pre-split path runs), rounded up to 256 bytes; 0 when the chosen
- * configuration needs none.  Same validation as gemm_plain (no memory is
+/* Device workspace bytes to hold for gemm_plain of this problem (split-K
+ * partial slabs of split*m*n float32, plus the split-BF16x3 or packed operand
+ * copies when those run), rounded up to 256 bytes; 0 when the chosen
+ * configuration needs none.  Slabs of up to GEMM_NOALLOC_SCRATCH_BYTES are
+ * counted also where the chosen configuration adds the ranges in the
+ * workgroup and leaves them unused.  Same validation as gemm_plain (no memory is
  * touched); the configuration lookup may read the device's compute-unit
  * count. */
 int gemm_plain_workspace_bytes(const gemm_problem_t *p, uint64_t *bytes_out);
@@ -134,8 +145,8 @@ int gemm_plain_workspace_bytes(const gemm_problem_t *p, uint64_t *bytes_out);
 /* Allocation-free plain product, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid allocation).  Same tile configuration, split-K factor and bits as
- * gemm_plain; the workspace gemm_plain_workspace_bytes reports comes from a
- * fixed device array of GEMM_NOALLOC_SCRATCH_BYTES that each GPU holds from
+ * gemm_plain (a product whose packed copies do not fit runs without them);
+ * the workspace comes from a fixed device array of GEMM_NOALLOC_SCRATCH_BYTES that each GPU holds from
  * the library's load until the process ends, instead of the per-stream
  * workspace.  No call allocates or frees device memory (the first call on a
  * device looks the array's address up once).  Errors: as gemm_plain, plus
@@ -362,7 +373,8 @@ typedef struct gemm_serve_stats {
 /* Admission footprint of a request under the batched executors (0, 1):
  * bytes(A) + bytes(B) + 4*m*n (grouped launches and a batch of one use no
  * workspace).  The plain-launch executor (2) admits each request by that
- * plus gemm_plain_workspace_bytes(p), the workspace of its plain launch. */
+ * plus gemm_plain_workspace_bytes(p) less any packed copies (it makes none),
+ * the workspace of its plain launch. */
 int gemm_serve_footprint(const gemm_problem_t *p, uint64_t *bytes_out);
 int gemm_serve_create(const gemm_serve_config_t *cfg, void **server_out);
 /* Enqueue one request (copied); returns a monotonic ticket.  GEMM_ENOMEM if

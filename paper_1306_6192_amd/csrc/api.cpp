@@ -130,7 +130,7 @@ Launch make_launch(const gemm_problem_t &p, const KernelCfg &kc, int split) {
     P.ldb = p.ldb;
     P.ldc = p.ldc;
     P.m = (int32_t)p.m;
-    P.n = (int32_t)p.n;
+    P.n = P.nb = (int32_t)p.n;
     P.k = (int32_t)p.k;
     P.tiles_m = (int32_t)((p.m + kc.bm - 1) / kc.bm);
     P.tiles_n = (int32_t)((p.n + kc.bn - 1) / kc.bn);
@@ -172,6 +172,63 @@ bool cfg_eligible(const gemm_problem_t &p, const KernelCfg &kc) {
            (uintptr_t)p.A % 16 == 0 && (uintptr_t)p.B % 16 == 0;
 }
 
+// The packed copies (pack.hip) that let a chunked configuration run a problem
+// whose operands are not whole 16-byte chunks.
+struct PackPlan {
+    bool a = false, b = false;       // which operands are copied
+    int64_t a_ld = 0, b_ld = 0;      // row strides of the copies, in elements
+    int64_t a_bytes = 0, b_bytes = 0;
+    int64_t bytes() const { return a_bytes + b_bytes; }
+};
+
+// Bytes of the interleaved operand copies of the pre-split path (A' then B',
+// each 256-byte aligned).
+static int64_t presplit_bytes(const gemm_problem_t &p, int64_t *b_off) {
+    const int64_t k16 = (p.k + 15) / 16 * 16, n8 = (p.n + 7) / 8 * 8;
+    const int64_t a = ((int64_t)p.m * 3 * k16 * 2 + 255) / 256 * 256;
+    *b_off = a;
+    return a + ((int64_t)3 * k16 * n8 * 2 + 255) / 256 * 256;
+}
+
+// The copies pay where each packed element is used often enough and the
+// register-staged tile is far behind: from about 512 rows, columns and k for
+// the 16- and 8-bit forms (ragged bfloat16 with the shortest output side in
+// [512, 1024): 0.74 to 1.67 times the speed of the best tile without copies,
+// above 2048 up to 2.4 times), from 2048 rows and columns for FP32, whose
+// 4-byte direct loads already take any shape (0.9 to 1.09 times below).
+// Bounded, since the workspace is kept: larger copies are left to the
+// register-staged tiles.
+static int64_t pack_min(int mode) { return mode == GEMM_MODE_F32 ? 2048 : 512; }
+static const int64_t kPackMaxBytes = (int64_t)512 << 20;
+
+static bool pack_plan(const gemm_problem_t &p, const KernelCfg &kc, PackPlan *plan) {
+    if ((kc.chunk == 0 && !kc.presplit) || cfg_eligible(p, kc)) return false;
+    if (p.m < pack_min(p.mode) || p.n < pack_min(p.mode) || p.k < 512) return false;
+    if (kc.presplit) {
+        // ragged n: the interleaved copies are made all the same, B's rows
+        // padded to eight columns (enqueue_plain makes and sizes them)
+        int64_t b_off = 0;
+        *plan = PackPlan();
+        return presplit_shape_ok((p.n + 7) / 8 * 8, p.k) && presplit_bytes(p, &b_off) <= kPackMaxBytes;
+    }
+    const int64_t c = kc.chunk, es = 16 / c;
+    PackPlan q;
+    q.a = p.k % c || p.lda % c || (uintptr_t)p.A % 16;
+    q.b = p.n % c || p.ldb % c || (uintptr_t)p.B % 16;
+    q.a_ld = q.a ? (p.k + c - 1) / c * c : p.lda;
+    q.b_ld = q.b ? (p.n + c - 1) / c * c : p.ldb;
+    if (q.a) q.a_bytes = (p.m * q.a_ld * es + 255) / 256 * 256;
+    if (q.b) q.b_bytes = (p.k * q.b_ld * es + 255) / 256 * 256;
+    if (q.bytes() > kPackMaxBytes) return false;
+    *plan = q;
+    return true;
+}
+
+bool cfg_runs(const gemm_problem_t &p, const KernelCfg &kc) {
+    PackPlan plan;
+    return cfg_eligible(p, kc) || pack_plan(p, kc, &plan);
+}
+
 int effective_cfg(const gemm_problem_t &p, int cfg) {
     int count = 0;
     const KernelCfg *t = configs(p.mode, &count);
@@ -194,21 +251,13 @@ int effective_cfg(const gemm_problem_t &p, int cfg) {
     return best;
 }
 
-// Bytes of the interleaved operand copies of the pre-split path (A' then B',
-// each 256-byte aligned).
-static int64_t presplit_bytes(const gemm_problem_t &p, int64_t *b_off) {
-    const int64_t k16 = (p.k + 15) / 16 * 16;
-    const int64_t a = ((int64_t)p.m * 3 * k16 * 2 + 255) / 256 * 256;
-    *b_off = a;
-    return a + ((int64_t)3 * k16 * p.n * 2 + 255) / 256 * 256;
-}
-
-int64_t plain_ws_bytes(const gemm_problem_t &p, int cfg, int split) {
+int64_t plain_ws_bytes(const gemm_problem_t &p, int cfg, int split, bool pack) {
     int count = 0;
     const KernelCfg *t = configs(p.mode, &count);
     if (!t || cfg < 0 || cfg >= count || p.m == 0 || p.n == 0 || p.k == 0) return 0;
-    const KernelCfg &kc = t[effective_cfg(p, cfg)];
-    int64_t ws = (make_launch(p, kc, split).ws_bytes + 255) / 256 * 256;
+    PackPlan plan;
+    const KernelCfg &kc = pack && pack_plan(p, t[cfg], &plan) ? t[cfg] : t[effective_cfg(p, cfg)];
+    int64_t ws = (make_launch(p, kc, split).ws_bytes + 255) / 256 * 256 + plan.bytes();
     if (kc.presplit) {
         int64_t b_off = 0;
         ws += presplit_bytes(p, &b_off);
@@ -216,7 +265,17 @@ int64_t plain_ws_bytes(const gemm_problem_t &p, int cfg, int split) {
     return ws;
 }
 
-int enqueue_plain(const gemm_problem_t &p, int cfg, int split, void *ws, hipStream_t s) {
+int64_t plain_ws_reported(const gemm_problem_t &p, int cfg, int split, bool pack) {
+    const int64_t used = plain_ws_bytes(p, cfg, split, pack);
+    int count = 0;
+    const KernelCfg *t = configs(p.mode, &count);
+    if (!t || cfg < 0 || cfg >= count || p.m == 0 || p.n == 0 || p.k == 0) return used;
+    const Launch L = make_launch(p, t[cfg], split);
+    const int64_t slabs = L.splits > 1 ? L.splits * L.P.split_stride * 4 : 0;
+    return std::max(used, (std::min(slabs, GEMM_NOALLOC_SCRATCH_BYTES) + 255) / 256 * 256);
+}
+
+int enqueue_plain(const gemm_problem_t &p, int cfg, int split, void *ws, hipStream_t s, bool pack) {
     if (p.m == 0 || p.n == 0) return GEMM_OK;
     if (p.k == 0) {
         MG_HIP(launch_fill_zero(p.C, p.ldc, (int)p.m, (int)p.n, s));
@@ -226,7 +285,9 @@ int enqueue_plain(const gemm_problem_t &p, int cfg, int split, void *ws, hipStre
     const KernelCfg *t = configs(p.mode, &count);
     if (!t || count == 0) return fail(GEMM_EUNSUPPORTED, "mode %d has no kernels", p.mode);
     if (cfg < 0 || cfg >= count) return fail(GEMM_EINVAL, "config %d out of range [0,%d)", cfg, count);
-    cfg = effective_cfg(p, cfg);
+    PackPlan plan;
+    pack = pack && pack_plan(p, t[cfg], &plan);
+    if (!pack) cfg = effective_cfg(p, cfg);
     Launch L = make_launch(p, t[cfg], split);
     const bool slabs = L.ws_bytes > 0;
     if (slabs) {
@@ -248,10 +309,26 @@ int enqueue_plain(const gemm_problem_t &p, int cfg, int split, void *ws, hipStre
         L.P.A = Ap;
         L.P.B = Bp;
         L.P.lda = 3 * k16;
-        L.P.ldb = p.n;
+        L.P.ldb = L.P.nb = (int32_t)((p.n + 7) / 8 * 8);
         L.P.k = (int32_t)(3 * k16);
         L.P.kt_per_split = L.P.kt_per_split * 3;
         L.P.vec = 3;
+    } else if (pack) {
+        // the operands' copies after the split-K slabs
+        if (!ws) return fail(GEMM_EINTERNAL, "packing workspace missing");
+        const int64_t es = (int64_t)elem_size(p.mode);
+        uint8_t *Ap = static_cast<uint8_t *>(ws) + (L.ws_bytes + 255) / 256 * 256;
+        uint8_t *Bp = Ap + plan.a_bytes;
+        MG_HIP(launch_pack(p.A, p.lda * es, p.m, p.k * es, plan.a ? Ap : nullptr, p.B, p.ldb * es, p.k, p.n * es,
+                           plan.b ? Bp : nullptr, s));
+        if (plan.a) L.P.A = Ap;
+        if (plan.b) {
+            L.P.B = Bp;
+            L.P.nb = (int32_t)plan.b_ld;
+        }
+        L.P.lda = plan.a_ld;
+        L.P.ldb = plan.b_ld;
+        L.P.vec |= 3;
     }
     MG_HIP(t[cfg].plain(L.P, L.nwg, s));
     if (slabs)
@@ -263,8 +340,35 @@ int enqueue_plain(const gemm_problem_t &p, int cfg, int split, void *ws, hipStre
 // ---------------------------------------------------------------------------
 // Device buffers.
 
+// Buffers replaced while their stream was being captured: graphs captured
+// before may hold their addresses, so they stay allocated.
+static std::mutex g_retired_mu;
+static std::vector<void *> g_retired;
+
 int DevBuf::ensure(size_t need, hipStream_t s) {
     if (need <= bytes) return GEMM_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        cap = hipStreamCaptureStatusNone;
+    }
+    const bool capturing = cap == hipStreamCaptureStatusActive;
+    // under capture an allocation (which enqueues nothing) needs the relaxed
+    // mode, and a stream that is being captured cannot be waited for
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (capturing) MG_HIP(hipThreadExchangeStreamCaptureMode(&mode));
+    struct Restore {
+        hipStreamCaptureMode *mode;
+        ~Restore() {
+            if (mode) (void)hipThreadExchangeStreamCaptureMode(mode);
+        }
+    } restore{capturing ? &mode : nullptr};
+    if (ptr && capturing) {
+        std::lock_guard<std::mutex> lk(g_retired_mu);
+        g_retired.push_back(ptr);
+        ptr = nullptr;
+        bytes = 0;
+    }
     if (ptr) {
         MG_HIP(hipStreamSynchronize(s));
         MG_HIP(hipFree(ptr));
@@ -395,20 +499,32 @@ static int plain_common(const gemm_problem_t *p, int cfg, int split, void *strea
     hipStream_t s = (hipStream_t)stream;
     if (p->m == 0 || p->n == 0) return GEMM_OK;
     void *ws = nullptr;
-    std::unique_lock<std::mutex> ws_lock = lock_stream_workspaces(s);
+    bool pack = true;
+    std::unique_lock<std::mutex> ws_lock;
     if (p->k > 0) {
         int count = 0;
         configs(p->mode, &count);
         if (count == 0) return fail(GEMM_EUNSUPPORTED, "mode %d has no kernels", p->mode);
-        const int64_t need = plain_ws_bytes(*p, cfg, split);
+        int64_t need = plain_ws_bytes(*p, cfg, split, true);
         if (need > 0) {
+            ws_lock = lock_stream_workspaces(s);
             DevBuf *b = stream_workspace(s, 0);
             rc = b->ensure((size_t)need, s);
+            if (rc == GEMM_ENOMEM) {
+                // without the packed copies (the register-staged tiles give
+                // the same bits)
+                const int64_t less = plain_ws_bytes(*p, cfg, split, false);
+                if (less < need) {
+                    clear_error();
+                    pack = false;
+                    rc = less > 0 ? b->ensure((size_t)less, s) : GEMM_OK;
+                }
+            }
             if (rc != GEMM_OK) return rc;
             ws = b->ptr;
         }
     }
-    return enqueue_plain(*p, cfg, split, ws, s);
+    return enqueue_plain(*p, cfg, split, ws, s, pack);
 }
 
 int gemm_plain(const gemm_problem_t *p, void *stream) {
@@ -441,7 +557,7 @@ int gemm_plain_workspace_bytes(const gemm_problem_t *p, uint64_t *bytes_out) {
     if (p->m == 0 || p->n == 0 || p->k == 0) return GEMM_OK;
     int cfg = 0, split = 1;
     tuner_choose(p->mode, p->m, p->n, p->k, &cfg, &split);
-    *bytes_out = (uint64_t)plain_ws_bytes(*p, cfg, split);
+    *bytes_out = (uint64_t)plain_ws_reported(*p, cfg, split, true);
     return GEMM_OK;
 }
 
@@ -454,12 +570,18 @@ int gemm_plain_noalloc(const gemm_problem_t *p, void *stream) {
     if (p->m == 0 || p->n == 0) return GEMM_OK;
     int cfg = 0, split = 1;
     void *ws = nullptr;
+    bool pack = true;
     if (p->k > 0) {
         int count = 0;
         configs(p->mode, &count);
         if (count == 0) return fail(GEMM_EUNSUPPORTED, "mode %d has no kernels", p->mode);
         tuner_choose(p->mode, p->m, p->n, p->k, &cfg, &split);
-        const int64_t need = plain_ws_bytes(*p, cfg, split);
+        int64_t need = plain_ws_bytes(*p, cfg, split, true);
+        if (need > GEMM_NOALLOC_SCRATCH_BYTES) {
+            // without the packed copies (same bits)
+            pack = false;
+            need = plain_ws_bytes(*p, cfg, split, false);
+        }
         if (need > GEMM_NOALLOC_SCRATCH_BYTES)
             return fail(GEMM_EINVAL,
                         "this product needs %lld bytes of workspace; gemm_plain_noalloc holds at most %lld "
@@ -470,7 +592,7 @@ int gemm_plain_noalloc(const gemm_problem_t *p, void *stream) {
             if (rc != GEMM_OK) return rc;
         }
     }
-    return enqueue_plain(*p, cfg, split, ws, (hipStream_t)stream);
+    return enqueue_plain(*p, cfg, split, ws, (hipStream_t)stream, pack);
 }
 
 int gemm_convert_f32(const float *x, int64_t count, int32_t to_mode, void *out, void *stream) {

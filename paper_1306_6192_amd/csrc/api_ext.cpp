@@ -139,7 +139,7 @@ static int enqueue_ext(int mode, int64_t m, int64_t n, int64_t k, const void *A,
     P.ldb = ldb;
     P.ldc = ldc;
     P.m = (int32_t)m;
-    P.n = (int32_t)n;
+    P.n = P.nb = (int32_t)n;
     P.k = (int32_t)k;
     P.tiles_m = (int32_t)((m + kc.bm - 1) / kc.bm);
     P.tiles_n = (int32_t)((n + kc.bn - 1) / kc.bn);

@@ -36,6 +36,7 @@ struct TileProblem {
     int32_t vec;             // bit0: A rows 16-B loadable, bit1: B rows, bit2: C rows
     float scale;             // epilogue multiplier (FP8: scale_a*scale_b; else 1)
     int64_t split_stride;    // elements between split-K partial slabs
+    int32_t nb;              // columns of B that may be loaded (n, or its padding included)
 };
 
 // Map a hardware workgroup id onto a logical tile id so that consecutive

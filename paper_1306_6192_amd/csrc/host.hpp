@@ -48,19 +48,25 @@ Launch make_launch(const gemm_problem_t &p, const KernelCfg &kc, int split);
 
 // Enqueue one plain product with an explicit configuration.  `ws` must hold
 // `Launch::ws_bytes` when the split is above 1.
-int enqueue_plain(const gemm_problem_t &p, int cfg, int split, void *ws, hipStream_t s);
+int enqueue_plain(const gemm_problem_t &p, int cfg, int split, void *ws, hipStream_t s, bool pack = false);
 
 // Whether the problem's shape, strides and alignment meet the configuration's
 // chunk requirement, and the configuration actually run for it: a chunked
 // configuration the problem does not meet is replaced by the any-shape one of
 // the same tile size (both sum every element in the same order).
 bool cfg_eligible(const gemm_problem_t &p, const KernelCfg &kc);
+// ... or can run on packed copies of the operands.
+bool cfg_runs(const gemm_problem_t &p, const KernelCfg &kc);
 bool presplit_shape_ok(int64_t n, int64_t k);
 int split_grain(int mode);
 int effective_cfg(const gemm_problem_t &p, int cfg);
 
-// Split-K workspace bytes the (cfg, split) choice needs for this problem.
-int64_t plain_ws_bytes(const gemm_problem_t &p, int cfg, int split);
+// Workspace bytes the (cfg, split) choice uses for this problem: split-K slabs
+// that go through memory, pre-split operand copies and (`pack`) packed ones.
+int64_t plain_ws_bytes(const gemm_problem_t &p, int cfg, int split, bool pack = false);
+// What a caller is told to hold: the same, and at least the slabs of the split
+// factor (up to 64 MB), also where a fused configuration adds them in LDS.
+int64_t plain_ws_reported(const gemm_problem_t &p, int cfg, int split, bool pack);
 
 // Tuning table.
 void tuner_choose(int mode, int64_t m, int64_t n, int64_t k, int *cfg, int *split);

@@ -40,7 +40,8 @@ struct KernelCfg {
     // split-BF16x3 only: the float32 operands are first split into an
     // interleaved bfloat16 copy (A' = [lo hi hi], B' = [hi; lo; hi] per 16 k)
     // and the product runs as one BF16 product over 3 x k16 (`plain` is then
-    // a BF16 kernel).  Needs n a multiple of 8; any k, strides, alignment.
+    // a BF16 kernel).  Any k, strides and alignment; a ragged n (not a multiple
+    // of 8) only where the copies may be made for it (pack_plan).
     int presplit;
     // > 0: each of the workgroup's waves (this many) runs a k range of the
     // split factor.  A factor up to that is added in LDS (no partial slabs,
@@ -91,10 +92,15 @@ hipError_t launch_ew_add(int elem_bytes, const void *A, int64_t lda, const void 
 hipError_t launch_zero_rows(void *C, int64_t ld_bytes, int m, int64_t row_bytes, hipStream_t s);
 // The interleaved bfloat16 operands of the pre-split split-BF16x3 path
 // (presplit.hip): A (m x k float32, lda) -> Ap (m x 3 k16, row stride 3 k16);
-// B (k x n float32, ldb) -> Bp (3 k16 x n, row stride n); k16 = k rounded up
-// to 16, the padding zero.
+// B (k x n float32, ldb) -> Bp (3 k16 x n8, row stride n8); k16 = k rounded up
+// to 16 and n8 = n rounded up to 8, the padding zero.
 hipError_t launch_presplit(const float *A, int64_t lda, const float *B, int64_t ldb, int m, int n, int k,
                            uint16_t *Ap, uint16_t *Bp, hipStream_t s);
+// Copies of A and/or B (a null destination: not copied) whose rows are whole
+// 16-byte chunks, zeros behind the last element (pack.hip); strides and row
+// lengths in bytes, destination rows contiguous and 16-byte aligned.
+hipError_t launch_pack(const void *A, int64_t lda_bytes, int64_t a_rows, int64_t a_row_bytes, void *Ap, const void *B,
+                       int64_t ldb_bytes, int64_t b_rows, int64_t b_row_bytes, void *Bp, hipStream_t s);
 // `bytes` (a multiple of 16) from pinned host memory to device memory, both
 // 16-byte aligned (misc.hip).
 hipError_t launch_upload(void *dst, const void *pinned, int64_t bytes, hipStream_t s);

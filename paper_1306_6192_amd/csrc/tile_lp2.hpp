@@ -217,7 +217,7 @@ __device__ __forceinline__ void lp2_sources(const TileProblem &P, int m0, int n0
             const int slot = 64 * (wave * Cfg::B_LOADS + j) + lane;
             const int kr = slot / Cfg::B_CPR;
             const int c = (slot % Cfg::B_CPR) ^ Cfg::b_swz(kr);
-            const int n = Cfg::REG ? n0 + c * Cfg::CE : min(n0 + c * Cfg::CE, P.n - Cfg::CE);
+            const int n = Cfg::REG ? n0 + c * Cfg::CE : min(n0 + c * Cfg::CE, P.nb - Cfg::CE);
             if constexpr (Cfg::REG) S.bcols[j] = P.n - n;
             S.bk[j] = kr;
             S.b[j] = B + ((int64_t)kr * P.ldb + n) * Cfg::ESZ;

@@ -233,10 +233,10 @@ static int time_choice(const gemm_problem_t &p, int cfg, int split, void *ws, hi
     MG_HIP(hipEventCreate(&e1));
     const int reps = 5;
     float ts[reps];
-    int rc = enqueue_plain(p, cfg, split, ws, s);  // warm-up
+    int rc = enqueue_plain(p, cfg, split, ws, s, true);  // warm-up
     for (int r = 0; r < reps && rc == GEMM_OK; ++r) {
         (void)hipEventRecord(e0, s);
-        rc = enqueue_plain(p, cfg, split, ws, s);
+        rc = enqueue_plain(p, cfg, split, ws, s, true);
         (void)hipEventRecord(e1, s);
         if (hipEventSynchronize(e1) != hipSuccess) rc = fail(GEMM_EHIP, "event sync failed");
         (void)hipEventElapsedTime(&ts[r], e0, e1);
@@ -333,7 +333,7 @@ static int tune_plain(int32_t mode, int64_t m, int64_t n, int64_t k, void *strea
     p.ldc = n;
     p.scale_a = p.scale_b = 1.f;
     for (int c = 0; c < count; ++c)
-        for (int sp = 1; sp <= 16; sp *= 2) ws_need = std::max(ws_need, plain_ws_bytes(p, c, sp));
+        for (int sp = 1; sp <= 16; sp *= 2) ws_need = std::max(ws_need, plain_ws_bytes(p, c, sp, true));
     int rc = GEMM_OK;
     if (hipMalloc(&A, (size_t)m * k * es) != hipSuccess || hipMalloc(&B, (size_t)k * n * es) != hipSuccess ||
         hipMalloc(&C, (size_t)m * n * 4) != hipSuccess ||
@@ -357,11 +357,11 @@ static int tune_plain(int32_t mode, int64_t m, int64_t n, int64_t k, void *strea
         p.B = B;
         p.C = static_cast<float *>(C);
         for (int c = 0; c < count && rc == GEMM_OK; ++c) {
-            if (!cfg_eligible(p, t[c])) continue;
+            if (!cfg_runs(p, t[c])) continue;
             const int64_t nkt = (k + split_grain(mode) - 1) / split_grain(mode);
             int last_split = 0;
             for (int sp = 1; sp <= 16 && rc == GEMM_OK; sp *= 2) {
-                if (sp > 1 && nkt / sp < 4) break;
+                if (sp > 1 && nkt / sp < (t[c].fused ? 1 : 4)) break;
                 const int eff = make_launch(p, t[c], sp).splits;
                 if (eff == last_split) continue;
                 last_split = eff;

@@ -1,4 +1,5 @@
-"""Tiles with waves along k against the register-staged tiles.
+"""Tiles with waves along k, and aligned operand copies, against the
+register-staged tiles.
 
 Every configuration of a mode sums an element in the same order for a given
 split-K factor, so these are bitwise comparisons with configuration 0 (itself
@@ -75,3 +76,56 @@ def test_every_config_equals_the_first_on_nan_padded_operands(mode, m, n, k):
             for x, y in ((a, b), (whole_a, whole_b), (ragged_a, ragged_b)):
                 got = product(x, y, mode, m, n, cfg=cfg, split_k=split)
                 assert np.array_equal(got, want), (cfg, split, x.stride(), y.stride())
+
+
+# just above the smallest sizes that are copied (512; FP32 2048), ragged in k,
+# in n, in both; whole chunks on a misaligned base
+PACKED = [(512, 513, 515), (600, 520, 513), (515, 1000, 520), (520, 528, 528)]
+
+
+@pytest.mark.parametrize("m,n,k", PACKED)
+@pytest.mark.parametrize("mode", MODES, ids=[_lib.MODE_NAMES[m] for m in MODES])
+def test_copied_operands_give_the_same_bits(mode, m, n, k):
+    """Configurations of whole chunks on ragged products: A, B or both are
+    copied to aligned rows.  Also without an explicit configuration, and
+    through the allocation-free entry point."""
+    if mode == mg.MODE_F32:
+        m, n, k = m + 1540, n + 1540, k
+    log(f"packed {_lib.MODE_NAMES[mode]} {(m, n, k)}")
+    a, b = operands(mode, m, n, k, seed=m + n + k)
+    views = ((a, b), (in_nan(a, mode, 1, 2), b), (a, in_nan(b, mode, 3, 2)), (in_nan(a, mode, 5, 1), in_nan(b, mode, 1, 1)))
+    want = product(a, b, mode, m, n, cfg=0, split_k=2)
+    for cfg in range(mg.num_configs(mode)):
+        if mg.config_chunk(mode, cfg) or mode == mg.MODE_SPLIT_BF16X3:
+            for x, y in views:
+                assert np.array_equal(product(x, y, mode, m, n, cfg=cfg, split_k=2), want), (cfg, x.stride(), y.stride())
+    chosen = product(a, b, mode, m, n)
+    for x, y in views:
+        assert np.array_equal(product(x, y, mode, m, n), chosen), (x.stride(), y.stride())
+    import ctypes
+    out = torch.full((m, n), float("nan"), device="cuda")
+    p = mg.make_problem(views[3][0], views[3][1], out, mode)
+    _lib.check(_lib.load().gemm_plain_noalloc(ctypes.byref(p), torch.cuda.current_stream().cuda_stream))
+    assert np.array_equal(host(out).view(np.uint32), chosen)
+
+
+def test_capture_of_a_product_that_needs_a_workspace():
+    """A ragged product (operand copies) and a split one captured on a stream
+    that has no workspace yet: the graph's replays equal the eager results,
+    also after eager work on other data in between."""
+    log("capture with copies and slabs")
+    cases = []
+    for mode, m, n, k in ((mg.MODE_BF16, 600, 1029, 1031), (mg.MODE_F32, 100, 3000, 5000)):
+        a, b = operands(mode, m, n, k, seed=m)
+        cases.append((mode, a, b, torch.empty((m, n), device="cuda"), host(mg.gemm(a, b, mode=mode))))
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=torch.cuda.Stream()):
+        for mode, a, b, out, _ in cases:
+            mg.gemm(a, b, out=out, mode=mode)
+    for _ in range(3):
+        for _, _, _, out, _ in cases:
+            out.fill_(float("nan"))
+        mg.gemm(torch.rand((700, 1031), device="cuda"), torch.rand((1031, 900), device="cuda"))
+        g.replay()
+        for _, _, _, out, want in cases:
+            assert np.array_equal(host(out), want)
