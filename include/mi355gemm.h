@@ -336,7 +336,9 @@ int gemm_tune_grouped(int32_t mode, int64_t m, int64_t n, int64_t k, void *strea
  * faster.  Synchronises.  Errors: as gemm_grouped, plus GEMM_EHIP. */
 int gemm_tune_grouped_mix(const gemm_problem_t *ps, int32_t count, void *stream);
 /* The (cfg, split_k) gemm_plain would use for this shape: the exact entry,
- * else the bucket entry, else the cost model. */
+ * else the bucket entry, else the choice of the nearest point of the table's
+ * measured grid (shapes of whole 16-byte chunks and ragged ones apart), else
+ * the cost model. */
 int gemm_tuner_lookup(int32_t mode, int64_t m, int64_t n, int64_t k, int32_t *cfg, int32_t *split_k);
 int gemm_tuner_load(const char *path);
 int gemm_tuner_save(const char *path);

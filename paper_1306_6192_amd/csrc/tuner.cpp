@@ -32,6 +32,20 @@ static double g_grouped_eff[GEMM_NUM_MODES] = {-1, -1, -1, -1, -1};   // small-t
 static int g_grouped_variant[GEMM_NUM_MODES] = {-1, -1, -1, -1, -1};  // grouped kernel variant (< 0: unset)
 static bool g_env_loaded = false;
 
+// The measured grid: the choice at every combination of the points 32, 48, 64,
+// 96, ... 8192 (2^b and 1.5 2^b) of m, n and k, for shapes of whole 16-byte
+// chunks (split-BF16x3: n a multiple of 8) and for ragged ones.  A shape takes
+// the choice of the nearest points (in log distance; dimensions beyond the
+// ends take the end).  Measured per point because the best tile turns with
+// each factor of 1.4: on 5000 drawn shapes the choices by log2 bucket and cost
+// model were 1.3 to 2.1 times slower (geometric means by mode) than the best
+// configuration, those of the nearest of 500 measured shapes 1.02 to 1.08.
+constexpr int GRID_POINTS = 17;
+struct GridChoice {
+    int16_t cfg = -1, split = 1;
+};
+static GridChoice g_grid[GEMM_NUM_MODES][2][GRID_POINTS][GRID_POINTS][GRID_POINTS];
+
 int dim_bucket(int64_t d) {
     int b = 0;
     while (d > 1) {
@@ -39,6 +53,24 @@ int dim_bucket(int64_t d) {
         ++b;
     }
     return b;
+}
+
+// Index of the grid point nearest to d: 2^b up to sqrt(1.5) 2^b, 1.5 2^b up to
+// sqrt(3) 2^b, then 2^(b+1).
+static int grid_point(int64_t d) {
+    if (d <= 32) return 0;
+    const int b = dim_bucket(d);
+    if (b >= 13) return GRID_POINTS - 1;
+    const int64_t sq = d * d, base = (int64_t)1 << (2 * b);
+    return 2 * (b - 5) + (2 * sq < 3 * base ? 0 : sq < 3 * base ? 1 : 2);
+}
+
+// Whether k and n are whole 16-byte chunks of the mode's asynchronous-copy
+// tiles (split-BF16x3: whether n is, for its operand copies).
+static int grid_class(int mode, int64_t n, int64_t k) {
+    if (mode == GEMM_MODE_F32_SPLIT_BF16X3) return n % 8 == 0;
+    const int64_t c = 16 / (int64_t)elem_size(mode);
+    return k % c == 0 && n % c == 0;
 }
 
 static BKey bucket_of(int mode, int64_t m, int64_t n, int64_t k) {
@@ -127,6 +159,22 @@ void tuner_choose(int mode, int64_t m, int64_t n, int64_t k, int *cfg, int *spli
             *split = ib->second.second;
             return;
         }
+        if (mode_known(mode)) {
+            const int cl = grid_class(mode, n, k), im = grid_point(m), in = grid_point(n), ik = grid_point(k);
+            GridChoice c = g_grid[mode][cl][im][in][ik];
+            // binary16 runs on the same tiles as bfloat16, at the same rates
+            if (c.cfg < 0 && mode == GEMM_MODE_F16) c = g_grid[GEMM_MODE_BF16][cl][im][in][ik];
+            if (c.cfg >= 0) {
+                int count = 0;
+                const KernelCfg &kc = configs(mode, &count)[c.cfg];
+                *cfg = c.cfg;
+                *split = c.split;
+                // (beyond the grid's ends the slabs could grow without bound)
+                const int in_wg = std::max(1, kc.fused);
+                if (*split > in_wg && (double)*split * (double)m * (double)n * 4.0 > 67108864.0) *split = in_wg;
+                return;
+            }
+        }
     }
     heuristic_choose(mode, m, n, k, cfg, split);
 }
@@ -164,12 +212,14 @@ int tuner_grouped_variant(int mode) {
     return mode_known(mode) && g_grouped_variant[mode] >= 0 ? g_grouped_variant[mode] : 0;
 }
 
-// One JSON object per line, in one of four forms (the forms gemm_tuner_save
+// One JSON object per line, in one of five forms (the forms gemm_tuner_save
 // writes; lines in any other form are skipped):
 //   {"mode": M, "m": m, "n": n, "k": k, "cfg": C, "split": S}
 //   {"bucket": "plain", "mode": M, "bm": a, "bn": b, "bk": c, "cfg": C, "split": S}
 //   {"bucket": "grouped", "mode": M, "bm": a, "bn": b, "bk": c, "alone": U}
 //   {"grouped_eff": M, "eff": E, "variant": V}  (", variant" optional: 0)
+//   {"grid": M, "whole": W, "m": i, "n": j, "choices": "C:S C:S ..."}
+//     (grid point indices i of m and j of n; one choice per point of k)
 static int load_file_locked(const char *path) {
     FILE *f = fopen(path, "r");
     if (!f) return fail(GEMM_ENOTFOUND, "cannot open tuning file %s", path);
@@ -179,7 +229,28 @@ static int load_file_locked(const char *path) {
         int mode, cfg, split, bm, bn, bk;
         long long m, n, k;
         int count = 0;
-        if (sscanf(line, " {\"mode\": %d, \"m\": %lld, \"n\": %lld, \"k\": %lld, \"cfg\": %d, \"split\": %d",
+        int at = 0;
+        if (sscanf(line, " {\"grid\": %d, \"whole\": %d, \"m\": %d, \"n\": %d, \"choices\": \"%n", &mode, &split, &bm, &bn,
+                   &at) == 4 &&
+            at > 0) {
+            if (!mode_known(mode) || split < 0 || split > 1 || bm < 0 || bm >= GRID_POINTS || bn < 0 || bn >= GRID_POINTS)
+                continue;
+            configs(mode, &count);
+            const char *c = line + at;
+            for (int i = 0; i < GRID_POINTS; ++i) {
+                char *end = nullptr;
+                const long cf = strtol(c, &end, 10);
+                if (end == c || *end != ':') break;
+                c = end + 1;
+                const long sp = strtol(c, &end, 10);
+                if (end == c) break;
+                c = end;
+                if (cf < 0 || cf >= count || sp < 1 || sp > 4096) continue;
+                g_grid[mode][split][bm][bn][i].cfg = (int16_t)cf;
+                g_grid[mode][split][bm][bn][i].split = (int16_t)sp;
+                ++n_ok;
+            }
+        } else if (sscanf(line, " {\"mode\": %d, \"m\": %lld, \"n\": %lld, \"k\": %lld, \"cfg\": %d, \"split\": %d",
                    &mode, &m, &n, &k, &cfg, &split) == 6) {
             if (!mode_known(mode)) continue;
             configs(mode, &count);
@@ -292,6 +363,19 @@ int gemm_tuner_save(const char *path) {
                 "\"split\": %d}\n",
                 std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first), std::get<3>(kv.first),
                 kv.second.first, kv.second.second);
+    for (int mode = 0; mode < GEMM_NUM_MODES; ++mode)
+        for (int whole = 0; whole < 2; ++whole)
+            for (int i = 0; i < GRID_POINTS; ++i)
+                for (int j = 0; j < GRID_POINTS; ++j) {
+                    const GridChoice *row = g_grid[mode][whole][i][j];
+                    int known = 0;
+                    for (int q = 0; q < GRID_POINTS; ++q) known += row[q].cfg >= 0;
+                    if (!known) continue;
+                    fprintf(f, "{\"grid\": %d, \"whole\": %d, \"m\": %d, \"n\": %d, \"choices\": \"", mode, whole, i, j);
+                    for (int q = 0; q < GRID_POINTS; ++q)   // (a point not measured: -1:1, skipped on loading)
+                        fprintf(f, "%s%d:%d", q ? " " : "", row[q].cfg, row[q].split);
+                    fprintf(f, "\"}\n");
+                }
     for (auto &kv : g_grouped)
         fprintf(f, "{\"bucket\": \"grouped\", \"mode\": %d, \"bm\": %d, \"bn\": %d, \"bk\": %d, \"alone\": %d}\n",
                 std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first), std::get<3>(kv.first),

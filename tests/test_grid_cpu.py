@@ -1,0 +1,117 @@
+"""The measured grid of the tuning table, without a GPU: which point a shape
+takes, its class (whole 16-byte chunks or ragged), what comes before it, and
+its file form.  Each case loads its own table in a process of its own."""
+import json
+import math
+import os
+import subprocess
+import sys
+
+from paper_1306_6192_amd import _lib
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+POINTS = [32, 48] + [p << s for s in range(1, 8) for p in (32, 48)] + [8192]
+
+LOOKUP = """
+import ctypes, json, sys
+sys.path.insert(0, %r)
+from paper_1306_6192_amd import _lib
+lib = _lib.load()
+def look(mode, m, n, k):
+    c, s = ctypes.c_int32(), ctypes.c_int32()
+    _lib.check(lib.gemm_tuner_lookup(mode, m, n, k, ctypes.byref(c), ctypes.byref(s)))
+    return c.value, s.value
+out = [look(*q) for q in json.loads(sys.argv[1])]
+if len(sys.argv) > 2:
+    _lib.check(lib.gemm_tuner_save(sys.argv[2].encode()))
+print(json.dumps(out))
+"""
+
+
+def lookups(table, shapes, save=None):
+    env = dict(os.environ, MI355GEMM_TUNE_FILE=str(table))
+    cmd = [sys.executable, "-c", LOOKUP % ROOT, json.dumps(shapes)] + ([str(save)] if save else [])
+    r = subprocess.run(cmd, env=env, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+    return [tuple(x) for x in json.loads(r.stdout.strip().splitlines()[-1])]
+
+
+def line(mode, whole, i, j, choices):
+    return ('{"grid": %d, "whole": %d, "m": %d, "n": %d, "choices": "' % (mode, whole, i, j)
+            + " ".join("%d:%d" % c for c in choices) + '"}\n')
+
+
+def nearest(d):
+    if d <= 32:
+        return 0
+    return min(range(len(POINTS)), key=lambda i: abs(math.log(d) - math.log(POINTS[i])))
+
+
+def test_every_dimension_takes_the_nearest_point(tmp_path):
+    """k alone decides here (one row of the grid): the split written at point q
+    is q + 1, so the lookup tells the point; all k around every turn."""
+    f = tmp_path / "t.jsonl"
+    f.write_text("".join(line(_lib.MODE_F32, w, 0, 0, [(6, q + 1) for q in range(len(POINTS))]) for w in (0, 1)))
+    ks = sorted({max(1, int(p * r) + d) for p in POINTS for r in (1, math.sqrt(1.5), math.sqrt(4 / 3)) for d in (-1, 0, 1, 2)}
+                | {1, 2, 31, 100000, 1 << 29})
+    got = lookups(f, [(_lib.MODE_F32, 20, 30, k) for k in ks])
+    assert [g[0] for g in got] == [6] * len(ks)
+    assert [g[1] - 1 for g in got] == [nearest(k) for k in ks]
+
+
+def test_class_and_order_of_the_table(tmp_path):
+    """Whole chunks and ragged shapes have choices of their own (split-BF16x3:
+    by n alone); an exact entry, then a bucket entry, come before the grid;
+    F16 takes BF16's grid until it has one; a point not measured, an unknown
+    configuration and a mode without a grid fall to the cost model."""
+    n17 = len(POINTS)
+    f = tmp_path / "t.jsonl"
+    rows = [line(_lib.MODE_BF16, 1, 2, 2, [(3, 2)] * n17), line(_lib.MODE_BF16, 0, 2, 2, [(4, 1)] * n17),
+            line(_lib.MODE_SPLIT_BF16X3, 1, 2, 2, [(2, 2)] * n17), line(_lib.MODE_SPLIT_BF16X3, 0, 2, 2, [(1, 1)] * n17),
+            line(_lib.MODE_F8E4M3, 1, 2, 2, [(-1, 1), (9999, 1)] + [(5, 4)] * (n17 - 2)),
+            '{"grid": 1, "whole": 2, "m": 0, "n": 0, "choices": "1:1"}\n', '{"grid": 1, "whole": 1, "m": 17, "n": 0, "choices": "1:1"}\n',
+            '{"mode": 1, "m": 64, "n": 64, "k": 1000, "cfg": 0, "split": 3}\n',
+            '{"bucket": "plain", "mode": 1, "bm": 6, "bn": 6, "bk": 11, "cfg": 1, "split": 5}\n']
+    f.write_text("".join(rows))
+    B, H, S, Q = _lib.MODE_BF16, _lib.MODE_F16, _lib.MODE_SPLIT_BF16X3, _lib.MODE_F8E4M3
+    got = lookups(f, [(B, 64, 64, 64), (B, 64, 68, 64), (B, 64, 64, 65), (H, 64, 64, 64), (H, 64, 66, 64), (S, 64, 64, 65),
+                      (S, 64, 65, 64), (B, 64, 64, 1000), (B, 65, 64, 1000), (B, 64, 64, 2048), (Q, 64, 64, 64)])
+    assert got == [(3, 2), (4, 1), (4, 1), (3, 2), (4, 1), (2, 2), (1, 1), (0, 3), (3, 2), (1, 5), (5, 4)]
+    other = lookups(f, [(Q, 64, 64, 32), (Q, 64, 64, 48), (_lib.MODE_F32, 64, 64, 64)])
+    empty = tmp_path / "e.jsonl"
+    empty.write_text("")
+    assert other == lookups(empty, [(Q, 64, 64, 32), (Q, 64, 64, 48), (_lib.MODE_F32, 64, 64, 64)])
+
+
+def test_grid_survives_save_and_load(tmp_path):
+    f, g = tmp_path / "t.jsonl", tmp_path / "saved.jsonl"
+    text = line(_lib.MODE_F32, 1, 3, 16, [(q % 5, 1 << (q % 7)) for q in range(len(POINTS))])
+    f.write_text(text)
+    a = lookups(f, [(_lib.MODE_F32, 96, 8192, p) for p in POINTS], save=g)
+    assert text in g.read_text()
+    assert lookups(g, [(_lib.MODE_F32, 96, 8192, p) for p in POINTS]) == a
+
+
+def test_shipped_grid_is_complete_and_slabs_are_bounded():
+    """Every point of the shipped table has a choice, and no shape, however
+    large, is given slabs above what gemm_plain_noalloc holds."""
+    seen = {}
+    with open(os.path.join(ROOT, "paper_1306_6192_amd", "tuning", "mi355x.jsonl")) as f:
+        for ln in f:
+            if ln.startswith('{"grid"'):
+                d = json.loads(ln)
+                seen[(d["grid"], d["whole"], d["m"], d["n"])] = [tuple(map(int, c.split(":"))) for c in d["choices"].split()]
+    for mode in (_lib.MODE_F32, _lib.MODE_BF16, _lib.MODE_F8E4M3, _lib.MODE_SPLIT_BF16X3):
+        for w in (0, 1):
+            for i in range(len(POINTS)):
+                for j in range(len(POINTS)):
+                    assert len(seen[(mode, w, i, j)]) == len(POINTS) and min(c for c, _ in seen[(mode, w, i, j)]) >= 0
+    lib = _lib.load()
+    import ctypes
+    info = (ctypes.c_int32 * 6)()
+    for mode in (_lib.MODE_F32, _lib.MODE_BF16, _lib.MODE_F16, _lib.MODE_F8E4M3):
+        for m, n, k in ((1 << 20, 33, 4096), (40, 1 << 22, 8192), (100000, 100000, 100), (16, 1 << 26, 512), (8192, 8192, 1 << 25)):
+            c, s = ctypes.c_int32(), ctypes.c_int32()
+            _lib.check(lib.gemm_tuner_lookup(mode, m, n, k, ctypes.byref(c), ctypes.byref(s)))
+            _lib.check(lib.gemm_config_info(mode, c, info))
+            assert s.value == 1 or s.value <= info[3] or s.value * m * n * 4 <= _lib.NOALLOC_SCRATCH_BYTES
