@@ -62,12 +62,23 @@ def make_problem(A, B, C, mode=MODE_F32, scale_a=1.0, scale_b=1.0):
                         C.data_ptr() or None, _ld(C), scale_a, scale_b)
 
 
+def _done(r):
+    """The result of a native call, or its error status raised."""
+    if type(r) is int:
+        check(r)
+    return r
+
+
 def gemm(A, B, out=None, mode=MODE_F32, scale_a=1.0, scale_b=1.0, cfg=None, split_k=None, stream=None):
     """C = A @ B (float32 result) for device matrices A (m x k) and B (k x n).
 
     ``mode`` selects the arithmetic form; A and B must hold the matching
     element type (float32, bfloat16, float16 or E4M3 codes).  ``cfg`` and
     ``split_k`` override the tuning table."""
+    if cfg is None and split_k is None and stream is None:
+        C = _lib.fastcall().gemm(A, B, out, mode, scale_a, scale_b)
+        if C is not None:
+            return _done(C)
     torch = _torch()
     _check_mat(A, "A", mode)
     _check_mat(B, "B", mode)
@@ -94,6 +105,10 @@ def gemm(A, B, out=None, mode=MODE_F32, scale_a=1.0, scale_b=1.0, cfg=None, spli
 
 def _gemm_same_type(A, B, out, dtype, entry, cfg, stream):
     torch = _torch()
+    if cfg is None and stream is None and getattr(A, "dtype", None) is dtype:
+        C = _lib.fastcall().gemm_same(A, B, out)
+        if C is not None:
+            return _done(C)
     for t, name in ((A, "A"), (B, "B")):
         _check_mat(t, name)
         if t.dtype != dtype:
@@ -167,6 +182,10 @@ def paper_kernel(A, B, out=None, variant=1, stream=None):
 
 def convert(x, mode, stream=None):
     """float32 -> bfloat16 / float16 codes (RNE), as a tensor of that dtype."""
+    if stream is None:
+        out = _lib.fastcall().convert(x, mode)
+        if out is not None:
+            return _done(out)
     torch = _torch()
     if x.dtype != torch.float32 or not x.is_cuda or not x.is_contiguous():
         raise ValueError("x must be a contiguous float32 device tensor")
@@ -179,6 +198,10 @@ def convert(x, mode, stream=None):
 
 def quantize_e4m3(x, stream=None):
     """Per-tensor E4M3 quantisation: returns (codes uint8, scale float32 device tensor of 1)."""
+    if stream is None:
+        qs = _lib.fastcall().quantize(x)
+        if qs is not None:
+            return _done(qs)
     torch = _torch()
     if x.dtype != torch.float32 or not x.is_cuda or not x.is_contiguous():
         raise ValueError("x must be a contiguous float32 device tensor")

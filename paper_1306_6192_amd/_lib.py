@@ -126,6 +126,7 @@ _SIGS = {
 }
 
 _lib = None
+_fast = None
 
 
 def load():
@@ -147,6 +148,21 @@ def load():
             lib.gemm_tuner_load(table.encode())
         _lib = lib
     return _lib
+
+
+def fastcall():
+    """The native call path of the Python layer's small entry points, bound to
+    the loaded library (raises if it is not built, like :func:`load`)."""
+    global _fast
+    if _fast is None:
+        import torch  # noqa: F401  (its libraries are the module's)
+        lib = load()
+        from . import _fastcall
+        _fastcall.bind(*(ctypes.cast(getattr(lib, name), c_void_p).value
+                         for name in ("gemm_plain", "gemm_plain_f64", "gemm_plain_c32", "gemm_convert_f32",
+                                      "gemm_quantize_e4m3")))
+        _fast = _fastcall
+    return _fast
 
 
 def last_error() -> str:

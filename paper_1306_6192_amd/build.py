@@ -4,7 +4,8 @@ Every source under ``csrc/`` (HIP kernels and the C++ host runtime) is
 compiled for gfx950 only and linked into one shared library that exports the
 C-ABI declared in ``include/mi355gemm.h``.  The compiler's per-kernel
 resource report (registers, scratch, occupancy, LDS) is kept in
-``_build/kernel_resources.txt``; a kernel that spills registers to scratch
+``_build/kernel_resources.txt``.  ``_fastcall.so``, the Python layer's native
+call path, is built beside the library.  A kernel that spills registers to scratch
 memory fails the build, since every tile is sized to fit its register budget.
 """
 from __future__ import annotations
@@ -20,6 +21,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libmi355gemm.so")
+FASTCALL = os.path.join(PKG, "_fastcall.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 COMMON = [
@@ -69,12 +71,36 @@ def _compile(src: str, verbose: bool):
     return obj, _resources(r.stderr)
 
 
+def _build_fastcall(verbose: bool) -> None:
+    """The Python layer's native call path (host code against torch's C++
+    headers; it is handed the library's entry points when it is loaded)."""
+    import sysconfig
+
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    tmp = FASTCALL + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+           "-DUSE_ROCM", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
+           "-I", os.path.join(tdir, "include"), "-I", os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+           "-I", "/opt/rocm/include", os.path.join(PKG, "csrc_py", "fastcall.cpp"), "-o", tmp,
+           "-L", os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), file=sys.stderr)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"building the native call path failed:\n{r.stderr}")
+    os.replace(tmp, FASTCALL)
+
+
 def build(verbose: bool = False, jobs: int | None = None) -> str:
     os.makedirs(BUILD, exist_ok=True)
     srcs = sources()
     jobs = jobs or min(len(srcs), max(1, min(8, os.cpu_count() or 1)))
     with cf.ThreadPoolExecutor(jobs) as ex:
+        fast = ex.submit(_build_fastcall, verbose)
         done = list(ex.map(lambda s: _compile(s, verbose), srcs))
+        fast.result()
     objs = [o for o, _ in done]
     kernels = sorted({k: v for _, res in done for k, v in res}.items())
     with open(os.path.join(BUILD, "kernel_resources.txt"), "w") as f:
