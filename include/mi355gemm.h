@@ -252,9 +252,9 @@ int gemm_errnorm(const float *C, int64_t ldc, const double *R, int64_t ldr,
 /* All problems must share one mode (F32 or BF16/F16/F8E4M3/split).  The
  * mode's grouped kernel is the variant the autotuner measured fastest on a
  * mixed batch (gemm_tune_grouped_mix; variant 0 when not measured): variant
- * 0 runs every problem on one 128 x 128 tile, variant 1 on 128 x 128 or
- * 64 x 64 by the cost model (all on the smaller one when the launch would
- * not fill the chip).  Every tile of a mode gives the same bits, so a
+ * 0 runs every problem on one 128 x 128 tile (all on 64 x 64 when the launch
+ * has few tiles), variant 1 on 128 x 128 or 64 x 64 by the cost model (all on
+ * the smaller one when the launch would not fill the chip).  Every tile of a mode gives the same bits, so a
  * problem's result does not depend on the other problems or the variant,
  * and equals gemm_plain's with split_k = 1.  The host builds a static schedule (gemm_grouped_schedule)
  * and uploads it with the descriptors into the (device, stream) pair's
@@ -275,8 +275,8 @@ int gemm_grouped_info(int32_t mode, int32_t info[7]);
  * of its own in the server (out[1]: the bucket's measured choice between the
  * two configurations of gemm_grouped_info's info[4..5], else the model),
  * and out[2] = 1 when both come from measurements (0: the model's defaults).
- * A two-tile launch whose problems would not fill every resident-workgroup
- * slot runs all of them on the smaller tile instead (see gemm_grouped_plan). */
+ * A launch of few tiles runs all of its problems on the smaller tile instead
+ * (see gemm_grouped_plan). */
 int gemm_grouped_lookup(int32_t mode, int64_t m, int64_t n, int64_t k, int32_t out[3]);
 
 /* The tile configuration each problem of this list gets in gemm_grouped

@@ -47,7 +47,7 @@ const KernelCfg *lp_configs_bf16(int *count) {
 }
 
 static const GroupedKernel kGrouped[2] = {
-    make_grouped_one<LpCfg<GEMM_MODE_BF16, 128, 128, 32>>(13, 13, 6, GROUPED_DEEP_16),
+    make_grouped_one<LpCfg<GEMM_MODE_BF16, 128, 128, 32>, LpCfg<GEMM_MODE_BF16, 64, 64>>(13, 13, 6, GROUPED_DEEP_16, GROUPED_SMALL_16),
     make_grouped<LpCfg<GEMM_MODE_BF16, 128, 128, 32>, LpCfg<GEMM_MODE_BF16, 64, 64>, GROUPED_TWO_OCC,
                  GROUPED_TWO_DEPTH>(13, 6, 13, 6)};
 

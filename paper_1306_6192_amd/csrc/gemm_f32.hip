@@ -70,8 +70,7 @@ const KernelCfg *f32_configs(int *count) {
 }
 
 static const GroupedKernel kF32Grouped[2] = {
-    make_grouped<F32Cfg<128, 128, 2, 2, 16>, F32Cfg<128, 128, 2, 2, 16>, GROUPED_ONE_OCC, GROUPED_ONE_DEPTH>(18, 18, 18,
-                                                                                                         24),
+    make_grouped_one<F32Cfg<128, 128, 2, 2, 16>, F32Cfg<64, 64, 2, 2, 32>>(18, 18, 24, 0.0, GROUPED_SMALL_F32),
     // (the 64 x 64 tile's accumulators share the 128 x 128 tile's first
     // block; the pair runs two workgroups per CU)
     make_grouped<F32Cfg<128, 128, 2, 2, 16>, F32Cfg<64, 64, 2, 2, 32>, GROUPED_TWO_OCC, GROUPED_ONE_DEPTH>(18, 24, 18,

@@ -32,7 +32,7 @@ const KernelCfg *lp_configs_f8(int *count) {
 }
 
 static const GroupedKernel kGrouped[2] = {
-    make_grouped_one<LpCfg<GEMM_MODE_F8E4M3, 128, 128, 64>>(11, 11, 6, GROUPED_DEEP_8),
+    make_grouped_one<LpCfg<GEMM_MODE_F8E4M3, 128, 128, 64>, LpCfg<GEMM_MODE_F8E4M3, 64, 64>>(11, 11, 6, GROUPED_DEEP_8, GROUPED_SMALL_8),
     make_grouped<LpCfg<GEMM_MODE_F8E4M3, 128, 128, 64>, LpCfg<GEMM_MODE_F8E4M3, 64, 64>, GROUPED_TWO_OCC,
                  GROUPED_TWO_DEPTH>(11, 6, 11, 6)};
 

@@ -61,7 +61,8 @@ const GroupedKernel *lp_grouped_split(int variant) {
     static const GroupedKernel k[2] = {
         [] {
             GroupedKernel g =
-                make_grouped_one<LpCfg<GEMM_MODE_F32_SPLIT_BF16X3, 128, 128, 16>>(0, 0, 5, GROUPED_DEEP_16);
+                make_grouped_one<LpCfg<GEMM_MODE_F32_SPLIT_BF16X3, 128, 128, 16>, LpCfg<GEMM_MODE_F32_SPLIT_BF16X3, 64, 64>>(0, 0, 5, GROUPED_DEEP_16,
+                                                                                     GROUPED_SMALL_SPLIT);
             g.cfg_idx[0] = g.cfg_idx[1] = g.alone_idx[0] = index_bk16();
             return g;
         }(),

@@ -120,11 +120,16 @@ static double tile_cost_us(int mode, const KernelCfg &kc, int64_t k, int wg_per_
 // whose tiles are placed one by one.  Within an XCD, tiles are dealt
 // costliest first over its workgroups in snake order.  The schedule depends
 // on the problem list only.
+// The plain configuration a descriptor's problem runs on.
+static int plan_cfg(const GroupPlan &plan, const GroupDesc &d) {
+    return plan.small ? plan.gk->small_idx : plan.gk->cfg_idx[d.cfg];
+}
+
 // Tile t of problem p (in the grouped row order of the plain launch: groups
 // of 8 tile rows, column by column within a group).
 static GroupTile tile_entry(const GroupPlan &plan, const KernelCfg *t, int p, int tile) {
     const GroupDesc &d = plan.descs[p];
-    const KernelCfg &kc = t[plan.gk->cfg_idx[d.cfg]];
+    const KernelCfg &kc = t[plan_cfg(plan, d)];
     const int group_m = 8;
     const int per_group = group_m * d.P.tiles_n;
     const int g = tile / per_group;
@@ -216,6 +221,7 @@ int build_group_plan(const gemm_problem_t *ps, int32_t count, GroupPlan &plan, i
     plan.wg_first.clear();
     plan.total_tiles = 0;
     plan.nwg = 0;
+    plan.small = plan.deep = false;
     plan.mode = count > 0 ? ps[0].mode : GEMM_MODE_F32;
     for (int i = 0; i < count; ++i) {
         int rc = validate(&ps[i]);
@@ -247,7 +253,11 @@ int build_group_plan(const gemm_problem_t *ps, int32_t count, GroupPlan &plan, i
         const KernelCfg &kc = t[plan.gk->cfg_idx[choice[i]]];
         chosen_tiles += ((p.m + kc.bm - 1) / kc.bm) * ((p.n + kc.bn - 1) / kc.bn);
     }
-    const int64_t slots = (int64_t)num_cus() * plan.gk->wg_per_cu;
+    // A one-tile kernel has a kernel of the smaller tile for such launches.
+    plan.small = force < 0 && plan.gk->launch_small &&
+                 (double)chosen_tiles < plan.gk->small_below * (double)num_cus();
+    const int wg_per_cu = plan.small ? plan.gk->small_per_cu : plan.gk->wg_per_cu;
+    const int64_t slots = (int64_t)num_cus() * wg_per_cu;
     const bool underfilled = force < 0 && chosen_tiles < slots;
     std::vector<double> cost;
     std::vector<int> ntiles;
@@ -262,19 +272,19 @@ int build_group_plan(const gemm_problem_t *ps, int32_t count, GroupPlan &plan, i
         GroupDesc d;
         memset(&d, 0, sizeof(d));
         d.cfg = underfilled ? small : choice[i];
-        const KernelCfg &kc = t[plan.gk->cfg_idx[d.cfg]];
+        const KernelCfg &kc = t[plan_cfg(plan, d)];
         d.P = make_launch(p, kc, 1).P;
         const int64_t nt = (int64_t)d.P.tiles_m * d.P.tiles_n;
         total += nt;
         if (total > INT32_MAX) return fail(GEMM_EUNSUPPORTED, "grouped launch above 2^31 tiles");
         plan.descs.push_back(d);
         plan.src.push_back(i);
-        cost.push_back(tile_cost_us(plan.mode, kc, p.k, plan.gk->wg_per_cu));
+        cost.push_back(tile_cost_us(plan.mode, kc, p.k, wg_per_cu));
         ntiles.push_back((int)nt);
     }
     plan.total_tiles = (int)total;
     plan.nwg = (int)std::min<int64_t>(total, slots);
-    plan.deep = plan.gk->launch_deep && (double)total < plan.gk->deep_below * (double)slots;
+    plan.deep = !plan.small && plan.gk->launch_deep && (double)total < plan.gk->deep_below * (double)slots;
     if (total > 0) build_schedule(plan, cost, ntiles);
     return GEMM_OK;
 }
@@ -306,7 +316,7 @@ int enqueue_group(const GroupPlan &plan, const void *dev_image, hipStream_t s) {
     G.wg_first = reinterpret_cast<const int32_t *>(d);
     d += align256(plan.wg_first.size() * sizeof(int32_t));
     G.tiles = reinterpret_cast<const GroupTile *>(d);
-    MG_HIP((plan.deep ? plan.gk->launch_deep : plan.gk->launch)(G, plan.nwg, s));
+    MG_HIP((plan.small ? plan.gk->launch_small : plan.deep ? plan.gk->launch_deep : plan.gk->launch)(G, plan.nwg, s));
     return GEMM_OK;
 }
 
@@ -615,7 +625,7 @@ int gemm_grouped_plan(const gemm_problem_t *ps, int32_t count, int32_t *cfg_out)
     int rc = build_group_plan(ps, count, plan);
     if (rc != GEMM_OK) return rc;
     for (int i = 0; i < count; ++i) cfg_out[i] = -1;
-    for (size_t j = 0; j < plan.descs.size(); ++j) cfg_out[plan.src[j]] = plan.gk->cfg_idx[plan.descs[j].cfg];
+    for (size_t j = 0; j < plan.descs.size(); ++j) cfg_out[plan.src[j]] = plan_cfg(plan, plan.descs[j]);
     return GEMM_OK;
 }
 

@@ -15,6 +15,7 @@ struct GroupPlan {
     std::vector<GroupTile> tiles;      // every workgroup's tile list, concatenated
     int total_tiles = 0;
     int nwg = 0;
+    bool small = false;                // the kernel of the smaller tile
     bool deep = false;                 // the kernel's form with one more k-tile in flight
 };
 

@@ -65,6 +65,12 @@ struct GroupedKernel {
     // than `deep_below` output tiles per resident workgroup (0: never).
     GroupedLaunchFn launch_deep;
     double deep_below;
+    // A kernel of one smaller tile (small_idx in the plain table, small_per_cu
+    // resident workgroups per CU) for launches of fewer than `small_below`
+    // tiles of the stream's own per CU (0: never).
+    GroupedLaunchFn launch_small;
+    int small_idx, small_per_cu;
+    double small_below;
 };
 
 // Tables of the configurations compiled for each mode (defined in the

@@ -39,6 +39,17 @@ template <int A, int B> struct cmax { static constexpr int v = A > B ? A : B; };
 // 25.6 -> 22.3, level at 1.6.  FP32, bound by its matrix pipe, gains nothing.
 constexpr int GROUPED_ONE_OCC = 3, GROUPED_ONE_DEPTH = 2;
 constexpr double GROUPED_DEEP_16 = 2.0, GROUPED_DEEP_8 = 1.5;
+// A launch of few 128x128 tiles runs on 64x64 tiles instead (four workgroups
+// per CU, two k-tiles in flight): one workgroup per CU cannot cover a step's
+// own chain of loads, LDS and MFMAs, four smaller ones do.  The lines are in
+// 128x128 tiles per CU, where a call's time stops gaining; a fuller launch
+// loses to the padding it saves less of and to the host's four times as many
+// schedule entries.  A call (us), 128x128 / 64x64: FP32 29 tiles 80 / 34, 324
+// tiles 95 / 48, 1266 tiles 153 / 128, level near 1900; split-BF16x3 29 tiles
+// 56 / 29, 464 tiles 63 / 38, level near 1000; bfloat16 29 tiles 27 / 16, 238
+// tiles 32 / 25, 464 tiles 33 / 35; E4M3 125 tiles 39 / 28, 238 tiles 22 / 25.
+constexpr int GROUPED_SMALL_OCC = 4, GROUPED_SMALL_DEPTH = 3;
+constexpr double GROUPED_SMALL_F32 = 5.0, GROUPED_SMALL_SPLIT = 2.5, GROUPED_SMALL_16 = 1.0, GROUPED_SMALL_8 = 0.6;
 constexpr int GROUPED_TWO_OCC = 2, GROUPED_TWO_DEPTH = 4;
 
 template <class Cfg, int OCC>
@@ -68,15 +79,27 @@ constexpr GroupedKernel make_grouped(int cfg0, int cfg1, int alone0, int alone1)
                          2 * GsRing<Cfg0, Cfg1>::STAGE,
                          launch_grouped_t<Cfg0, Cfg1, OCC, DEPTH>,
                          nullptr,
+                         0.0,
+                         nullptr,
+                         0,
+                         0,
                          0.0};
 }
 
-// A one-tile grouped kernel with its deeper form (see GROUPED_ONE_DEPTH).
-template <class Cfg>
-constexpr GroupedKernel make_grouped_one(int cfg, int alone0, int alone1, double deep_below) {
+// A one-tile grouped kernel with its deeper form (see GROUPED_ONE_DEPTH;
+// deep_below 0: none) and its smaller tile's kernel; `alone1` is that tile's
+// index in the plain table.
+template <class Cfg, class Small>
+constexpr GroupedKernel make_grouped_one(int cfg, int alone0, int alone1, double deep_below, double small_below) {
     GroupedKernel g = make_grouped<Cfg, Cfg, GROUPED_ONE_OCC, GROUPED_ONE_DEPTH>(cfg, cfg, alone0, alone1);
-    g.launch_deep = launch_grouped_t<Cfg, Cfg, GROUPED_ONE_OCC, GROUPED_ONE_DEPTH + 1>;
+    if (deep_below > 0.0) g.launch_deep = launch_grouped_t<Cfg, Cfg, GROUPED_ONE_OCC, GROUPED_ONE_DEPTH + 1>;
     g.deep_below = deep_below;
+    g.launch_small = launch_grouped_t<Small, Small, GROUPED_SMALL_OCC, GROUPED_SMALL_DEPTH>;
+    g.small_idx = alone1;
+    g.small_per_cu = (160 * 1024 / (2 * GsRing<Small, Small>::STAGE)) < GROUPED_SMALL_OCC
+                         ? (160 * 1024 / (2 * GsRing<Small, Small>::STAGE))
+                         : GROUPED_SMALL_OCC;
+    g.small_below = small_below;
     return g;
 }
 

@@ -224,16 +224,20 @@ def test_tune_grouped_mix_records_a_variant(tmp_path):
             _lib.check(lib.gemm_tuner_load(shipped.encode()))
 
 
-# 768 workgroups are resident: lists of one tile per problem just below and at
-# the 2 (E4M3: 1.5) tiles per workgroup from which the launch keeps one k-tile
-# in flight instead of two, and single-tile lists
-@pytest.mark.parametrize("count", [1, 2, 1151, 1152, 1535, 1536])
-@pytest.mark.parametrize("mode", [mg.MODE_BF16, mg.MODE_F16, mg.MODE_F8E4M3, mg.MODE_SPLIT_BF16X3],
-                         ids=["bf16", "f16", "e4m3", "split_bf16x3"])
-def test_grouped_either_depth_equals_plain(mode, count):
-    """The launch's two forms give the plain launch's bits: k below one
-    k-tile, one more than it, several; odd strides."""
-    log(f"grouped depth {mode} {count}")
+# lists of one 128x128 tile per problem on 256 CUs, just below and at the
+# counts where the launch turns from 64x64 tiles to 128x128 ones (0.6, 1, 2.5
+# and 5 tiles per CU by mode) and from two k-tiles in flight to one (1.5 or 2
+# tiles per resident workgroup of three a CU), and the shortest lists
+TURNS = [(mg.MODE_F32, (1, 1279, 1280)), (mg.MODE_SPLIT_BF16X3, (2, 639, 640, 1535, 1536)),
+         (mg.MODE_BF16, (1, 255, 256, 1535, 1536)), (mg.MODE_F16, (3, 255, 256, 1535, 1536)),
+         (mg.MODE_F8E4M3, (1, 153, 154, 1151, 1152))]
+
+
+@pytest.mark.parametrize("mode,count", [(m, c) for m, cs in TURNS for c in cs])
+def test_grouped_every_form_equals_plain(mode, count):
+    """The launch's forms give the plain launch's bits: k below one k-tile,
+    one more than it, several; odd strides."""
+    log(f"grouped form {mode} {count}")
     g = torch.Generator(device="cuda").manual_seed(count)
     ks = [1, 7, 33, 65, 129, 200, 300, 514]
     m, n = 31, 37
