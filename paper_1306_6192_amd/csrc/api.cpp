@@ -194,16 +194,21 @@ static int64_t presplit_bytes(const gemm_problem_t &p, int64_t *b_off) {
 // register-staged tile is far behind: from about 512 rows, columns and k for
 // the 16- and 8-bit forms (ragged bfloat16 with the shortest output side in
 // [512, 1024): 0.74 to 1.67 times the speed of the best tile without copies,
-// above 2048 up to 2.4 times), from 2048 rows and columns for FP32, whose
-// 4-byte direct loads already take any shape (0.9 to 1.09 times below).
+// above 2048 up to 2.4 times), from about 2048 rows and columns for FP32,
+// whose 4-byte direct loads already take any shape (0.9 to 1.09 times below).
+// The lines are where the tuner's measured points turn to 512 and to 2048,
+// so that all shapes of a point run the kind of launch that was measured for
+// it (with the lines at 512 and 2048 themselves the points' shapes just below
+// ran without copies, and 537 x 3262 x 5706 on their choice took 264 us; 64
+// on the choice measured with copies).
 // Bounded, since the workspace is kept: larger copies are left to the
 // register-staged tiles.
-static int64_t pack_min(int mode) { return mode == GEMM_MODE_F32 ? 2048 : 512; }
+static int64_t pack_min(int mode) { return mode == GEMM_MODE_F32 ? 1774 : 444; }
 static const int64_t kPackMaxBytes = (int64_t)512 << 20;
 
 static bool pack_plan(const gemm_problem_t &p, const KernelCfg &kc, PackPlan *plan) {
     if ((kc.chunk == 0 && !kc.presplit) || cfg_eligible(p, kc)) return false;
-    if (p.m < pack_min(p.mode) || p.n < pack_min(p.mode) || p.k < 512) return false;
+    if (p.m < pack_min(p.mode) || p.n < pack_min(p.mode) || p.k < 444) return false;
     if (kc.presplit) {
         // ragged n: the interleaved copies are made all the same, B's rows
         // padded to eight columns (enqueue_plain makes and sizes them)
