@@ -67,7 +67,7 @@ typedef enum {
  *                    loA hiB, hiA loB, hiA hiB.  The split happens at
  *                    tile staging, or (n a multiple of 8, or m, n and k at
  *                    least 444) once per operand into a library workspace of
- *                    6*k16*(m + n8) bytes, k16 = k rounded up to 16 and n8 = n
+ *                    4*k16*(m + n8) bytes, k16 = k rounded up to 16 and n8 = n
  *                    rounded up to 8; both give the same bits. */
 typedef enum {
     GEMM_MODE_F32 = 0,

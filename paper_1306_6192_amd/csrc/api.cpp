@@ -157,8 +157,9 @@ Launch make_launch(const gemm_problem_t &p, const KernelCfg &kc, int split) {
     return L;
 }
 
-// The pre-split path runs a BF16 product over an inner dimension of 3 k16
-// (k rounded up to 16), which the tile indexes with 32-bit integers.
+// The pre-split path's operand copies have an inner dimension of 2 k16 (k
+// rounded up to 16), which the tile indexes with 32-bit integers, k-tiles past
+// the end included.
 bool presplit_shape_ok(int64_t n, int64_t k) {
     const int64_t k16 = (k + 15) / 16 * 16;
     return n % 8 == 0 && n >= 8 && 3 * k16 <= (int64_t)INT32_MAX;
@@ -185,9 +186,9 @@ struct PackPlan {
 // each 256-byte aligned).
 static int64_t presplit_bytes(const gemm_problem_t &p, int64_t *b_off) {
     const int64_t k16 = (p.k + 15) / 16 * 16, n8 = (p.n + 7) / 8 * 8;
-    const int64_t a = ((int64_t)p.m * 3 * k16 * 2 + 255) / 256 * 256;
+    const int64_t a = ((int64_t)p.m * 2 * k16 * 2 + 255) / 256 * 256;
     *b_off = a;
-    return a + ((int64_t)3 * k16 * n8 * 2 + 255) / 256 * 256;
+    return a + ((int64_t)2 * k16 * n8 * 2 + 255) / 256 * 256;
 }
 
 // The copies pay where each packed element is used often enough and the
@@ -300,8 +301,8 @@ int enqueue_plain(const gemm_problem_t &p, int cfg, int split, void *ws, hipStre
         L.P.C = static_cast<float *>(ws);
     }
     if (t[cfg].presplit) {
-        // interleaved bfloat16 operands after the split-K slabs; the product
-        // runs over 3 k16 with three BF16 k-tiles per 32-k split grain
+        // the operands' hi and lo parts after the split-K slabs: 2 k16 elements
+        // per row of A and rows of B
         if (!ws) return fail(GEMM_EINTERNAL, "pre-split workspace missing");
         int64_t b_off = 0;
         presplit_bytes(p, &b_off);
@@ -313,10 +314,9 @@ int enqueue_plain(const gemm_problem_t &p, int cfg, int split, void *ws, hipStre
                                (int)p.m, (int)p.n, (int)p.k, Ap, Bp, s));
         L.P.A = Ap;
         L.P.B = Bp;
-        L.P.lda = 3 * k16;
+        L.P.lda = 2 * k16;
         L.P.ldb = L.P.nb = (int32_t)((p.n + 7) / 8 * 8);
-        L.P.k = (int32_t)(3 * k16);
-        L.P.kt_per_split = L.P.kt_per_split * 3;
+        L.P.k = (int32_t)(2 * k16);
         L.P.vec = 3;
     } else if (pack) {
         // the operands' copies after the split-K slabs

@@ -1,11 +1,12 @@
-// Split-BF16x3 product kernels (float32 operands split into bfloat16 hi/lo
-// planes at staging).  Two planes per operand in LDS, so the largest tile is
-// 256 x 128.
+// Split-BF16x3 product kernels: float32 operands split into bfloat16 hi/lo
+// planes at staging (two planes per operand in LDS, so the largest tile is
+// 256 x 128), and tiles on operands split once beforehand.
 #include <iterator>
 #include <vector>
 
 #include "kernels_impl.hpp"
 #include "tile_lp.hpp"
+#include "tile_lp2.hpp"
 
 static const KernelCfg kTable[] = {
     make_cfg<LpCfg<GEMM_MODE_F32_SPLIT_BF16X3, 256, 128>, 1>(), make_cfg<LpCfg<GEMM_MODE_F32_SPLIT_BF16X3, 128, 256>, 1>(),
@@ -13,32 +14,54 @@ static const KernelCfg kTable[] = {
     make_cfg<LpCfg<GEMM_MODE_F32_SPLIT_BF16X3, 64, 128>, 2>(),  make_cfg<LpCfg<GEMM_MODE_F32_SPLIT_BF16X3, 64, 64>, 4>(),
 };
 
-const KernelCfg *lp_configs_bf16(int *count);
-
-static KernelCfg presplit(KernelCfg k) {
-    k.chunk = 0;
+// The table entry of an asynchronous-copy tile on the operand copies (any
+// shape: the copies are padded); its k-tile is half as many k as elements.
+template <class Cfg, int OCC>
+static KernelCfg presplit() {
+    KernelCfg k = make_cfg<Cfg, OCC, 0, 1>();
+    k.bk /= 2;
+    return k;
+}
+template <class Cfg, int OCC>
+static KernelCfg presplit_fused() {
+    KernelCfg k = make_fused<Cfg, OCC>();
+    k.bk /= 2;
     k.presplit = 1;
     return k;
 }
 
-// The register-staged tiles above (any shape), then one pre-split entry per
-// asynchronous-copy BF16 tile with
-// k-tiles of 32: those run the split form as a BF16 product over interleaved
-// operand copies and give the same bits (the BF16 kernels themselves live in
-// the BF16 table).  A 32-k split-K grain of the split form is three such
-// k-tiles of the interleaved product; a k-tile of 64 would straddle grains.
-// Then the register-staged 128 x 128 tile with k-tiles of 16 (the grouped
-// launch's large tile), and the pre-split entries with waves along k.
+// (BM, BN, LDS stages, waves along m and n, bytes of an A row: 64 = 16 k, 128 =
+// 32 k; waves along k)
+template <int BM, int BN, int STAGES, int WM = 2, int WN = 2, int AROWB = 64, int WK = 0>
+using Spl = Lp2Cfg<GEMM_MODE_F32_SPLIT_BF16X3, BM, BN, STAGES, WM, WN, AROWB, 16, 32, WK>;
+
+static const KernelCfg kPresplit[] = {
+    presplit<Spl<256, 256, 4>, 1>(),
+    presplit<Spl<256, 128, 4>, 1>(),
+    presplit<Spl<128, 256, 4>, 1>(),
+    presplit<Spl<128, 128, 4>, 2>(),
+    // eight waves (two per SIMD)
+    presplit<Spl<256, 256, 4, 2, 4>, 2>(),
+    presplit<Spl<256, 256, 4, 4, 2>, 2>(),
+    // k-tiles of 32 in two stages
+    presplit<Spl<256, 128, 2, 2, 2, 128>, 1>(),
+    presplit<Spl<128, 256, 2, 2, 2, 128>, 1>(),
+    presplit<Spl<128, 128, 2, 2, 2, 128>, 2>(),
+    // the register-staged 128 x 128 tile with k-tiles of 16 (the grouped
+    // launch's large tile)
+    make_cfg<LpCfg<GEMM_MODE_F32_SPLIT_BF16X3, 128, 128, 16>, 3>(),
+    // waves along k
+    presplit_fused<Spl<32, 64, 2, 1, 1, 64, 8>, 2>(),
+    presplit_fused<Spl<64, 64, 2, 1, 1, 64, 8>, 2>(),
+};
+
+// The register-staged tiles (any shape), then the tiles on operand copies that
+// are split once (presplit.hip); the same products in the same order, so the
+// same bits.
 const KernelCfg *lp_configs_split(int *count) {
     static const std::vector<KernelCfg> table = [] {
         std::vector<KernelCfg> t(std::begin(kTable), std::end(kTable));
-        int nb = 0;
-        const KernelCfg *bf = lp_configs_bf16(&nb);
-        for (int c = 0; c < nb; ++c)
-            if (bf[c].chunk && bf[c].bk == 32 && !bf[c].fused) t.push_back(presplit(bf[c]));
-        t.push_back(make_cfg<LpCfg<GEMM_MODE_F32_SPLIT_BF16X3, 128, 128, 16>, 3>());
-        for (int c = 0; c < nb; ++c)
-            if (bf[c].chunk && bf[c].bk == 32 && bf[c].fused) t.push_back(presplit(bf[c]));
+        t.insert(t.end(), std::begin(kPresplit), std::end(kPresplit));
         return t;
     }();
     *count = (int)table.size();

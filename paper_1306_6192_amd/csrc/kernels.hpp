@@ -37,10 +37,9 @@ struct KernelCfg {
     // (`chunk` elements): k, n, lda and ldb must be multiples of it and A, B
     // 16-byte aligned.
     int chunk;
-    // split-BF16x3 only: the float32 operands are first split into an
-    // interleaved bfloat16 copy (A' = [lo hi hi], B' = [hi; lo; hi] per 16 k)
-    // and the product runs as one BF16 product over 3 x k16 (`plain` is then
-    // a BF16 kernel).  Any k, strides and alignment; a ragged n (not a multiple
+    // split-BF16x3 only: the float32 operands are first split into bfloat16
+    // copies (A' = [hi lo], B' = [hi; lo] per 16 k), over whose 2 k16 inner
+    // elements the product runs.  Any k, strides and alignment; a ragged n (not a multiple
     // of 8) only where the copies may be made for it (pack_plan).
     int presplit;
     // > 0: each of the workgroup's waves (this many) runs a k range of the
@@ -96,9 +95,9 @@ hipError_t launch_quantize_e4m3(const float *x, int64_t count, uint8_t *q, float
 hipError_t launch_ew_add(int elem_bytes, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
                          int64_t ldc, int m, int n, int subtract, hipStream_t s);
 hipError_t launch_zero_rows(void *C, int64_t ld_bytes, int m, int64_t row_bytes, hipStream_t s);
-// The interleaved bfloat16 operands of the pre-split split-BF16x3 path
-// (presplit.hip): A (m x k float32, lda) -> Ap (m x 3 k16, row stride 3 k16);
-// B (k x n float32, ldb) -> Bp (3 k16 x n8, row stride n8); k16 = k rounded up
+// The hi and lo bfloat16 parts of the pre-split split-BF16x3 path's operands
+// (presplit.hip): A (m x k float32, lda) -> Ap (m x 2 k16, row stride 2 k16);
+// B (k x n float32, ldb) -> Bp (2 k16 x n8, row stride n8); k16 = k rounded up
 // to 16 and n8 = n rounded up to 8, the padding zero.
 hipError_t launch_presplit(const float *A, int64_t lda, const float *B, int64_t ldb, int m, int n, int k,
                            uint16_t *Ap, uint16_t *Bp, hipStream_t s);

@@ -1,5 +1,5 @@
-// Asynchronous-copy output tile (BF16, F16, FP8, FP32, binary64 and complex
-// float).
+// Asynchronous-copy output tile (BF16, F16, FP8, split-BF16x3 on operand copies,
+// FP32, binary64 and complex float).
 //
 // Same arithmetic as the register-staged tiles (tile_lp.hpp for BF16, F16
 // and FP8, tile_f32.hpp for FP32, tile_f64.hpp for binary64, tile_c32.hpp
@@ -99,6 +99,15 @@ struct Lp2Cfg {
     static constexpr bool H16 = (MODE == GEMM_MODE_BF16 || MODE == GEMM_MODE_F16);
     static_assert(MB_ == 32 || (MB_ == 16 && H16), "16x16 blocks for the 16-bit tiles only");
     static constexpr bool M16 = H16 && MB_ == 16;      // 16x16x32 MFMAs
+    // split-BF16x3 on the operand copies of presplit.hip: 32 elements of an A
+    // row (rows of B) are the hi, then the lo parts of 16 k.  A step loads and
+    // reads the four kinds of fragments once for its three products: bound by
+    // LDS (reads and direct loads), 128 bytes a clock for the 128 x 128 tile,
+    // where the same products as one BF16 product over 3 k ([lo hi hi] by
+    // [hi; lo; hi]) move 192: 2048^3 70.2 -> 61.0 us a call, 4096^3 366 -> 331,
+    // 8192^3 2742 -> 2377 (1.39 PFLOP/s of BF16 products).
+    static constexpr bool SPL = (MODE == GEMM_MODE_F32_SPLIT_BF16X3);
+    static constexpr int PL = SPL ? 2 : 1;              // parts of an element in a step's fragments
     static constexpr int BLK = F64 ? 16 : MB_;          // accumulator block edge
     static constexpr int TM = BM / WM, TN = BN / WN;
     static constexpr int RB = TM / BLK, CB = TN / BLK;
@@ -110,13 +119,13 @@ struct Lp2Cfg {
     static constexpr int BK = A_ROWB / ESZ;             // k per k-tile
     // k per step: one MFMA (16- and 8-bit), four 32x32x2 MFMAs (FP32), four
     // 16x16x4 MFMAs (binary64), four times four 32x32x2 MFMAs (complex)
-    static constexpr int KCH = (MODE == GEMM_MODE_F8E4M3) ? 64 : F64 ? 16 : (F32 || C32) ? 8 : M16 ? 32 : 16;
-    static constexpr int MFMA_K = (F32 || C32) ? 2 : F64 ? 4 : KCH;
+    static constexpr int KCH = (MODE == GEMM_MODE_F8E4M3) ? 64 : F64 ? 16 : (F32 || C32) ? 8 : M16 || SPL ? 32 : 16;
+    static constexpr int MFMA_K = (F32 || C32) ? 2 : F64 ? 4 : SPL ? 16 : KCH;
     static constexpr int STEPS = BK / KCH;
     static constexpr bool FOUR = F32 || F64 || C32;     // four k-slots per block per step
-    static constexpr int NPB = FOUR ? 4 : CB;           // B fragment reads per step
-    static constexpr int NP = RB + NPB;                 // fragment reads per step
-    static constexpr int NM = RB * CB * (FOUR ? 4 : 1) * (C32 ? 4 : 1);   // MFMAs per step
+    static constexpr int NPB = FOUR ? 4 : PL * CB;      // B fragment reads per step
+    static constexpr int NP = PL * RB + NPB;            // fragment reads per step
+    static constexpr int NM = RB * CB * (FOUR ? 4 : SPL ? 3 : 1) * (C32 ? 4 : 1);   // MFMAs per step
     typedef typename std::conditional<F64, f64x4, typename std::conditional<M16, f32x4, f32x16>::type>::type Acc;
     static constexpr int B_ROWB = BN * ESZ;
     static constexpr int B_CPR = B_ROWB / 16;           // 16-byte chunks per B row
@@ -346,8 +355,8 @@ template <class Cfg,
 struct Lp2Frag;
 template <class Cfg>
 struct Lp2Frag<Cfg, 0> {
-    u32x4 a[Cfg::RB];
-    u32x4 b[Cfg::CB];
+    u32x4 a[Cfg::PL * Cfg::RB];
+    u32x4 b[Cfg::PL * Cfg::CB];
 };
 template <class Cfg>
 struct Lp2Frag<Cfg, 1> {
@@ -469,31 +478,42 @@ __device__ __forceinline__ void lp2_read_piece(const uint8_t *stage, int kc, int
             F.b[cb] = (u32x4){(uint32_t)lo[0], (uint32_t)lo[1], (uint32_t)hi[0], (uint32_t)hi[1]};
         }
     } else {
-        if (p < Cfg::RB) {
-            const int rb = p;
-            const int r = wm * Cfg::TM + rb * 32 + l32;
-            F.a[rb] = *reinterpret_cast<const u32x4 *>(As + r * Cfg::A_ROWB + 16 * ((2 * kc + g) ^ Cfg::a_swz(r)));
+        if (p < Cfg::PL * Cfg::RB) {
+            const int r = wm * Cfg::TM + p % Cfg::RB * 32 + l32, k16 = Cfg::PL * kc + p / Cfg::RB;
+            F.a[p] = *reinterpret_cast<const u32x4 *>(As + r * Cfg::A_ROWB + 16 * ((2 * k16 + g) ^ Cfg::a_swz(r)));
         } else {
-            const int cb = p - Cfg::RB;
-            const int n = wn * Cfg::TN + cb * 32 + 16 * (G & 1) + 4 * (p16 & 3);
+            const int q = p - Cfg::PL * Cfg::RB, k16 = Cfg::PL * kc + q / Cfg::CB;
+            const int n = wn * Cfg::TN + q % Cfg::CB * 32 + 16 * (G & 1) + 4 * (p16 & 3);
             s16x4 hv[2];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const int k = 16 * kc + 8 * (G >> 1) + 4 * h + (p16 >> 2);
+                const int k = 16 * k16 + 8 * (G >> 1) + 4 * h + (p16 >> 2);
                 const uint8_t *a = Bs + k * Cfg::B_ROWB + 16 * ((n >> 3) ^ Cfg::b_swz(k)) + 2 * (n & 7);
                 hv[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)a);
             }
             const i32x2 lo = __builtin_bit_cast(i32x2, hv[0]);
             const i32x2 hi = __builtin_bit_cast(i32x2, hv[1]);
-            F.b[cb] = (u32x4){(uint32_t)lo[0], (uint32_t)lo[1], (uint32_t)hi[0], (uint32_t)hi[1]};
+            F.b[q] = (u32x4){(uint32_t)lo[0], (uint32_t)lo[1], (uint32_t)hi[0], (uint32_t)hi[1]};
         }
     }
 }
 
+// Split-BF16x3: piece p (< RB + CB) of the fragments of a step's first product
+// (A lo, B hi) or of those its other products add (A hi, B lo).
+template <class Cfg, bool FIRST>
+__device__ __forceinline__ void lp2_read_part(const uint8_t *stage, int kc, int p, Lp2Frag<Cfg> &F) {
+    if (p < Cfg::RB) lp2_read_piece<Cfg>(stage, kc, (FIRST ? Cfg::RB : 0) + p, F);
+    else lp2_read_piece<Cfg>(stage, kc, Cfg::RB + (FIRST ? 0 : Cfg::CB) + p, F);
+}
+
+// The fragments a step starts with.
 template <class Cfg>
 __device__ __forceinline__ void lp2_read(const uint8_t *stage, int kc, Lp2Frag<Cfg> &F) {
 #pragma unroll
-    for (int p = 0; p < Cfg::NP; ++p) lp2_read_piece<Cfg>(stage, kc, p, F);
+    for (int p = 0; p < (Cfg::SPL ? Cfg::RB + Cfg::CB : Cfg::NP); ++p) {
+        if constexpr (Cfg::SPL) lp2_read_part<Cfg, true>(stage, kc, p, F);
+        else lp2_read_piece<Cfg>(stage, kc, p, F);
+    }
 }
 
 // MFMA i (0 .. NM-1) of one k-step.  16- and 8-bit: the one MFMA of
@@ -533,6 +553,13 @@ __device__ __forceinline__ void lp2_mfma1(const Lp2Frag<Cfg> &F, typename Cfg::A
         if constexpr (Cfg::CB == 1) bv = F.b[t];
         else bv = F.b[t][cb];
         acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(F.a[rb][t], bv, acc[rb][cb], 0, 0, 0);
+    } else if constexpr (Cfg::SPL) {
+        // every block's lo hi, then hi lo, then hi hi
+        constexpr int NB = Cfg::RB * Cfg::CB;
+        const int t = i / NB, rb = (i / Cfg::CB) % Cfg::RB, cb = i % Cfg::CB;
+        acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            __builtin_bit_cast(bf16x8, F.a[(t == 0 ? Cfg::RB : 0) + rb]),
+            __builtin_bit_cast(bf16x8, F.b[(t == 1 ? Cfg::CB : 0) + cb]), acc[rb][cb], 0, 0, 0);
     } else {
         const int rb = i / Cfg::CB, cb = i % Cfg::CB;
         if constexpr (Cfg::MODE == GEMM_MODE_F8E4M3)
@@ -587,6 +614,12 @@ __device__ __forceinline__ void lp2_epilogue16(float *__restrict__ C, int64_t ld
 //     and frees the stage just consumed), then the other half of the MFMAs
 //     interleaved with the reads of the next k-tile's first fragments and
 //     the refill of the freed stage with the k-tile STAGES ahead.
+// Split-BF16x3 has one form: the step's lo hi products, with the reads of its
+// other fragments (A hi, B lo) between them; its hi lo products; at a boundary
+// the wait and barrier above; its hi hi products, with the reads of the next
+// step's first fragments (A lo, B hi) and the refill.  So at most two of the
+// four kinds of fragments are held twice over (all four, as the other modes
+// hold theirs, spill in the eight-wave tiles).
 // Scheduling barriers pin this interleaving: the matrix cores then always
 // have an MFMA queued while the wave issues its reads and loads, and the
 // compiler cannot sink MFMAs below the workgroup barrier (they touch no
@@ -598,11 +631,46 @@ __device__ __forceinline__ void lp2_epilogue16(float *__restrict__ C, int64_t ld
 // same in every iteration.  CHECK selects the k-bounded form of the loads.
 template <class Cfg, bool BOUNDARY, bool CHECK>
 __device__ __forceinline__ void lp2_step(const Lp2Src<Cfg> &S, int kt0, int i, int u, int kc, uint8_t *lds,
-                                         const Lp2Frag<Cfg> &cur, Lp2Frag<Cfg> &nxt,
+                                         Lp2Frag<Cfg> &cur, Lp2Frag<Cfg> &nxt,
                                          typename Cfg::Acc (&acc)[Cfg::RB][Cfg::CBA], Lp2Reg<Cfg> *reg) {
     constexpr int NP = Cfg::NP;                     // fragment pieces per step
     constexpr int NM = Cfg::NM;                     // MFMAs per step
-    if constexpr (BOUNDARY) {
+    if constexpr (Cfg::SPL) {
+        constexpr int NB = Cfg::RB * Cfg::CB, NF = Cfg::RB + Cfg::CB;
+        constexpr int W = NF + (BOUNDARY ? Cfg::LOADS : 0);
+        constexpr int PER1 = (NF + NB - 1) / NB, PER3 = (W + NB - 1) / NB;
+        const uint8_t *here = lds + u * Cfg::STAGE;
+        const uint8_t *next = BOUNDARY ? lds + ((u + 1) % Cfg::STAGES) * Cfg::STAGE : here;
+        const int k0 = (kt0 + i + Cfg::STAGES) * Cfg::BK;
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+            lp2_mfma1<Cfg>(cur, acc, t);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int w = t * PER1; w < (t + 1) * PER1 && w < NF; ++w) lp2_read_part<Cfg, false>(here, kc, w, cur);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int t = NB; t < 2 * NB; ++t) lp2_mfma1<Cfg>(cur, acc, t);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (BOUNDARY) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            wait_vmcnt<(Cfg::STAGES - 2) * Cfg::LOADS>();
+            if constexpr (Cfg::WK) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            else __syncthreads();
+        }
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+            lp2_mfma1<Cfg>(cur, acc, 2 * NB + t);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int w = t * PER3; w < (t + 1) * PER3 && w < W; ++w) {
+                if (w < NF) lp2_read_part<Cfg, true>(next, BOUNDARY ? 0 : kc + 1, w, nxt);
+                else lp2_issue_one<Cfg, CHECK>(S, k0, u * Cfg::STAGE, w - NF);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else if constexpr (BOUNDARY) {
         // MFMAs before the barrier
         constexpr int H = Cfg::FOUR || Cfg::RB == 1 ? NM / 2 : ((Cfg::RB + 1) / 2) * Cfg::CB;
         constexpr int W = NP + (Cfg::REG ? 0 : Cfg::LOADS);   // work items after it

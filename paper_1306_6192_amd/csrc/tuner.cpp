@@ -107,10 +107,10 @@ void heuristic_choose(int mode, int64_t m, int64_t n, int64_t k, int *cfg_out, i
         if (kc.fused) continue;
         if (kc.chunk && (k % kc.chunk || n % kc.chunk)) continue;
         if (kc.presplit && !presplit_shape_ok(n, k)) continue;
-        // the pre-split split-BF16x3 path runs at about 1.75x the register-
+        // the pre-split split-BF16x3 path runs at about 1.8x the register-
         // staged split tile at 8192^3 (its operands are split once, not once
         // per output tile)
-        double bonus = kc.presplit ? 1.75 : 1.0;
+        double bonus = kc.presplit ? 1.8 : 1.0;
         if (kc.chunk) bonus = mode == GEMM_MODE_F32 ? 1.1 : 1.7;
         const int64_t tiles = ((m + kc.bm - 1) / kc.bm) * ((n + kc.bn - 1) / kc.bn);
         const int64_t nkt = (k + split_grain(mode) - 1) / split_grain(mode) * (split_grain(mode) / kc.bk);
