@@ -28,11 +28,10 @@ __device__ __forceinline__ void load8(const float *__restrict__ P, int64_t ld, i
 __device__ __forceinline__ void split8(const float (&v)[8], u32x4 &hi, u32x4 &lo) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        uint32_t h0, l0, h1, l1;
-        split_bf16(v[2 * e], h0, l0);
-        split_bf16(v[2 * e + 1], h1, l1);
-        hi[e] = h0 | (h1 << 16);
-        lo[e] = l0 | (l1 << 16);
+        uint32_t h, l;
+        split_bf16_pair(v[2 * e], v[2 * e + 1], h, l);
+        hi[e] = h;
+        lo[e] = l;
     }
 }
 
