@@ -115,3 +115,14 @@ def test_shipped_grid_is_complete_and_slabs_are_bounded():
             _lib.check(lib.gemm_tuner_lookup(mode, m, n, k, ctypes.byref(c), ctypes.byref(s)))
             _lib.check(lib.gemm_config_info(mode, c, info))
             assert s.value == 1 or s.value <= info[3] or s.value * m * n * 4 <= _lib.NOALLOC_SCRATCH_BYTES
+
+
+def test_slabs_are_bounded_by_fewer_ranges(tmp_path):
+    """A shape larger than its point takes as many ranges as 64 MB of slabs
+    hold, down to the ranges that need none."""
+    f = tmp_path / "t.jsonl"
+    f.write_text(line(_lib.MODE_F32, 0, 4, 16, [(6, 16)] * len(POINTS)) + line(_lib.MODE_F32, 0, 16, 16, [(6, 16)] * len(POINTS)))
+    shapes = [(_lib.MODE_F32, m, n, 8191) for m, n in ((128, 8191), (129, 8191), (147, 7867), (155, 9001), (8191, 8191))]
+    for (_, m, n, _), (cfg, split) in zip(shapes, lookups(f, shapes)):
+        slab = (m * n + 3) // 4 * 16
+        assert cfg == 6 and split == min(16, max(1, (64 << 20) // slab)), (m, n, split)
