@@ -35,6 +35,13 @@ static KernelCfg presplit_fused() {
 template <int BM, int BN, int STAGES, int WM = 2, int WN = 2, int AROWB = 64, int WK = 0>
 using Spl = Lp2Cfg<GEMM_MODE_F32_SPLIT_BF16X3, BM, BN, STAGES, WM, WN, AROWB, 16, 32, WK>;
 
+template <int BM, int BN, int WK>
+static KernelCfg fused_reg() {
+    KernelCfg k = make_fused<Lp2Cfg<GEMM_MODE_F32_SPLIT_BF16X3, BM, BN, 2, 1, 1, 64, 0, 32, WK>, 2>();
+    k.bk /= 2;
+    return k;
+}
+
 static const KernelCfg kPresplit[] = {
     presplit<Spl<256, 256, 4>, 1>(),
     presplit<Spl<256, 128, 4>, 1>(),
@@ -53,6 +60,12 @@ static const KernelCfg kPresplit[] = {
     // waves along k
     presplit_fused<Spl<32, 64, 2, 1, 1, 64, 8>, 2>(),
     presplit_fused<Spl<64, 64, 2, 1, 1, 64, 8>, 2>(),
+    // waves along k on the float32 operands themselves, split on their way into
+    // LDS (any shape; no copies, one launch)
+    fused_reg<32, 32, 4>(),
+    fused_reg<32, 32, 8>(),
+    fused_reg<32, 64, 8>(),
+    fused_reg<64, 64, 8>(),
 };
 
 // The register-staged tiles (any shape), then the tiles on operand copies that
@@ -73,7 +86,7 @@ static int index_bk16() {
     int n = 0, at = 0;
     const KernelCfg *t = lp_configs_split(&n);
     for (int c = 0; c < n; ++c)
-        if (t[c].bk == 16 && !t[c].presplit) at = c;
+        if (t[c].bk == 16 && !t[c].presplit && !t[c].fused) at = c;
     return at;
 }
 

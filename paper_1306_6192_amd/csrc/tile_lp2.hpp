@@ -137,6 +137,11 @@ struct Lp2Cfg {
     static constexpr int LDB = LDB_;                    // bytes per lane per direct load
     static constexpr bool REG = LDB == 0;               // 16-byte loads through registers
     static_assert(!REG || (WK > 0 && STAGES == 2), "two register sets and two stages of a wave's own");
+    // split-BF16x3 through registers: from the float32 operands themselves,
+    // split on their way into LDS (the same LDS image)
+    static constexpr bool SPLR = SPL && REG;
+    static constexpr int SRC_ESZ = SPLR ? 4 : ESZ, SRC_CE = 16 / SRC_ESZ;   // element and chunk in memory
+    static constexpr int KT = SPLR ? BK / 2 : BK;       // k of the operands per k-tile
     static constexpr int WLOAD = 64 * (REG ? 16 : LDB); // bytes one wave moves per load
     static_assert(REG || LDB == 16 || (LDB == 4 && (F32 || F64 || C32)),
                   "16-byte loads, or 4-byte loads of whole elements' words");
@@ -211,7 +216,24 @@ __device__ __forceinline__ void lp2_sources(const TileProblem &P, int m0, int n0
     const int wave = __builtin_amdgcn_readfirstlane(Cfg::WK ? 0 : threadIdx.x >> 6);
     const uint8_t *A = static_cast<const uint8_t *>(P.A);
     const uint8_t *B = static_cast<const uint8_t *>(P.B);
-    if constexpr (Cfg::LDB != 4) {
+    if constexpr (Cfg::SPLR) {
+        // loads 2 q and 2 q + 1: the eight floats of one hi and one lo chunk
+#pragma unroll
+        for (int j = 0; j < Cfg::A_LOADS; ++j) {
+            const int q = 64 * (j / 2) + lane;
+            const int row = min(m0 + q / (Cfg::A_CPR / 2), P.m - 1);
+            S.ak[j] = 8 * (q % (Cfg::A_CPR / 2)) + 4 * (j % 2);
+            S.a[j] = A + ((int64_t)row * P.lda + S.ak[j]) * 4;
+        }
+#pragma unroll
+        for (int j = 0; j < Cfg::B_LOADS; ++j) {
+            const int q = 64 * (j / 2) + lane;
+            const int n = n0 + 8 * (q % Cfg::B_CPR) + 4 * (j % 2);
+            S.bcols[j] = P.n - n;
+            S.bk[j] = q / Cfg::B_CPR;
+            S.b[j] = B + ((int64_t)S.bk[j] * P.ldb + n) * 4;
+        }
+    } else if constexpr (Cfg::LDB != 4) {
 #pragma unroll
         for (int j = 0; j < Cfg::A_LOADS; ++j) {
             const int t = wave * Cfg::A_LOADS + j;          // 1 KiB piece of the A stage
@@ -258,7 +280,7 @@ __device__ __forceinline__ void lp2_sources(const TileProblem &P, int m0, int n0
             S.b[j] = B + ((int64_t)kr * P.ldb + n) * Cfg::ESZ + o % Cfg::ESZ;
         }
     }
-    S.bstep = P.ldb * Cfg::ESZ;
+    S.bstep = P.ldb * Cfg::SRC_ESZ;
     S.kend = kend;
     const uint32_t base = lds_addr(lds);
     S.dst_a = base + Cfg::WLOAD * (wave * Cfg::A_LOADS);
@@ -305,15 +327,15 @@ struct Lp2Reg {
 template <class Cfg>
 __device__ __forceinline__ u32x4 lp2_chunk(const uint8_t *p, int have) {
     u32x4 v = {0u, 0u, 0u, 0u};
-    if (have >= Cfg::CE) {
+    if (have >= Cfg::SRC_CE) {
         v = ld16(p);
     } else if (have > 0) {
         uint8_t b[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) b[i] = 0;
 #pragma unroll
-        for (int e = 0; e < Cfg::CE; ++e)
-            if (e < have) __builtin_memcpy(b + e * Cfg::ESZ, p + e * Cfg::ESZ, Cfg::ESZ);
+        for (int e = 0; e < Cfg::SRC_CE; ++e)
+            if (e < have) __builtin_memcpy(b + e * Cfg::SRC_ESZ, p + e * Cfg::SRC_ESZ, Cfg::SRC_ESZ);
         __builtin_memcpy(&v, b, 16);
     }
     return v;
@@ -323,7 +345,7 @@ template <class Cfg, bool CHECK>
 __device__ __forceinline__ void lp2_load(const Lp2Src<Cfg> &S, int k0, Lp2Reg<Cfg> &R) {
 #pragma unroll
     for (int j = 0; j < Cfg::A_LOADS; ++j) {
-        const uint8_t *p = S.a[j] + (int64_t)k0 * Cfg::ESZ;
+        const uint8_t *p = S.a[j] + (int64_t)k0 * Cfg::SRC_ESZ;
         R.v[j] = CHECK ? lp2_chunk<Cfg>(p, S.kend - k0 - S.ak[j]) : ld16(p);
     }
 #pragma unroll
@@ -335,6 +357,36 @@ __device__ __forceinline__ void lp2_load(const Lp2Src<Cfg> &S, int k0, Lp2Reg<Cf
 
 template <class Cfg>
 __device__ __forceinline__ void lp2_land(const Lp2Reg<Cfg> &R, uint8_t *stage) {
+    if constexpr (Cfg::SPLR) {
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int j = 0; j < Cfg::LOADS; j += 2) {
+            u32x4 hi, lo;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                uint32_t h, l;
+                split_bf16_pair(__uint_as_float(R.v[j + e / 2][2 * (e % 2)]),
+                                __uint_as_float(R.v[j + e / 2][2 * (e % 2) + 1]), h, l);
+                hi[e] = h;
+                lo[e] = l;
+            }
+            if (j < Cfg::A_LOADS) {
+                const int q = 64 * (j / 2) + lane;
+                const int r = q / (Cfg::A_CPR / 2), c = q % (Cfg::A_CPR / 2);
+                uint8_t *row = stage + r * Cfg::A_ROWB;
+                *reinterpret_cast<u32x4 *>(row + 16 * ((4 * (c / 2) + c % 2) ^ Cfg::a_swz(r))) = hi;
+                *reinterpret_cast<u32x4 *>(row + 16 * ((4 * (c / 2) + c % 2 + 2) ^ Cfg::a_swz(r))) = lo;
+            } else {
+                const int q = 64 * ((j - Cfg::A_LOADS) / 2) + lane;
+                const int kr = q / Cfg::B_CPR, c = q % Cfg::B_CPR;
+                uint8_t *at = stage + Cfg::A_STAGE + (32 * (kr / 16) + kr % 16) * Cfg::B_ROWB +
+                              16 * (c ^ Cfg::b_swz(kr));
+                *reinterpret_cast<u32x4 *>(at) = hi;
+                *reinterpret_cast<u32x4 *>(at + 16 * Cfg::B_ROWB) = lo;
+            }
+        }
+        return;
+    }
     uint8_t *dst = stage + 16 * (threadIdx.x & 63);
 #pragma unroll
     for (int j = 0; j < Cfg::LOADS; ++j) *reinterpret_cast<u32x4 *>(dst + Cfg::WLOAD * j) = R.v[j];
@@ -637,7 +689,7 @@ __device__ __forceinline__ void lp2_step(const Lp2Src<Cfg> &S, int kt0, int i, i
     constexpr int NM = Cfg::NM;                     // MFMAs per step
     if constexpr (Cfg::SPL) {
         constexpr int NB = Cfg::RB * Cfg::CB, NF = Cfg::RB + Cfg::CB;
-        constexpr int W = NF + (BOUNDARY ? Cfg::LOADS : 0);
+        constexpr int W = NF + (BOUNDARY && !Cfg::REG ? Cfg::LOADS : 0);
         constexpr int PER1 = (NF + NB - 1) / NB, PER3 = (W + NB - 1) / NB;
         const uint8_t *here = lds + u * Cfg::STAGE;
         const uint8_t *next = BOUNDARY ? lds + ((u + 1) % Cfg::STAGES) * Cfg::STAGE : here;
@@ -654,8 +706,13 @@ __device__ __forceinline__ void lp2_step(const Lp2Src<Cfg> &S, int kt0, int i, i
         for (int t = NB; t < 2 * NB; ++t) lp2_mfma1<Cfg>(cur, acc, t);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (BOUNDARY) {
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            wait_vmcnt<(Cfg::STAGES - 2) * Cfg::LOADS>();
+            if constexpr (Cfg::REG) {
+                lp2_land<Cfg>(reg[(u + 1) % 2], lds + ((u + 1) % 2) * Cfg::STAGE);
+                lp2_load<Cfg, CHECK>(S, (kt0 + i + 3) * Cfg::KT, reg[(u + 1) % 2]);
+            } else {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                wait_vmcnt<(Cfg::STAGES - 2) * Cfg::LOADS>();
+            }
             if constexpr (Cfg::WK) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             else __syncthreads();
         }
@@ -769,7 +826,7 @@ __device__ __forceinline__ void lp2_tile(const TileProblem &P, int tm, int tn, i
     // the columns that are the tile's own)
     const int m0 = tm * Cfg::BM;
     const int n0 = Cfg::REG ? max(0, min(tn * Cfg::BN, P.n - Cfg::BN)) : tn * Cfg::BN;
-    const int nkt = (P.k + Cfg::BK - 1) / Cfg::BK;
+    const int nkt = (P.k + Cfg::KT - 1) / Cfg::KT;
     const int kt0 = split * P.kt_per_split;
     const int kt1 = min(kt0 + P.kt_per_split, nkt);
     const int nt = max(0, kt1 - kt0);
@@ -787,19 +844,19 @@ __device__ __forceinline__ void lp2_tile(const TileProblem &P, int tm, int tn, i
         // Fill the ring with k-tiles 0 .. STAGES-1 (those past kt1 read the
         // zero chunk; they are never used).
         Lp2Src<Cfg> S;
-        const int kend = min(P.k, kt1 * Cfg::BK);
+        const int kend = min(P.k, kt1 * Cfg::KT);
         lp2_sources<Cfg>(P, m0, n0, kend, lds, S);
         // k-tiles [0, nfull) of this split lie wholly before kend
-        int nfull = (kend - kt0 * Cfg::BK) / Cfg::BK;
+        int nfull = (kend - kt0 * Cfg::KT) / Cfg::KT;
         Lp2Reg<Cfg> reg_sets[Cfg::REG ? 2 : 1];
         Lp2Reg<Cfg> *reg = reg_sets;
         if constexpr (Cfg::REG) {
             // k-tile 0 to stage 0, k-tiles 1 and 2 in the registers
             if (P.n - n0 < Cfg::BN) nfull = 0;     // chunks that end past the last column
-            lp2_load<Cfg, true>(S, kt0 * Cfg::BK, reg[0]);
-            lp2_load<Cfg, true>(S, (kt0 + 1) * Cfg::BK, reg[1]);
+            lp2_load<Cfg, true>(S, kt0 * Cfg::KT, reg[0]);
+            lp2_load<Cfg, true>(S, (kt0 + 1) * Cfg::KT, reg[1]);
             lp2_land<Cfg>(reg[0], lds);
-            lp2_load<Cfg, true>(S, (kt0 + 2) * Cfg::BK, reg[0]);
+            lp2_load<Cfg, true>(S, (kt0 + 2) * Cfg::KT, reg[0]);
         } else {
 #pragma unroll
             for (int s = 0; s < Cfg::STAGES; ++s) lp2_issue<Cfg>(S, (kt0 + s) * Cfg::BK, s * Cfg::STAGE);
