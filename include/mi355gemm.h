@@ -65,8 +65,8 @@ typedef enum {
  *                    C = hiA hiB + hiA loB + loA hiB (compensated BF16),
  *                    the three products summed per 16 k in the order
  *                    loA hiB, hiA loB, hiA hiB.  The split happens at
- *                    tile staging, or (n a multiple of 8, or m, n and k at
- *                    least 444) once per operand into a library workspace of
+ *                    tile staging, or (n a multiple of 8, or m and n at
+ *                    least 157 and k 444) once per operand into a library workspace of
  *                    4*k16*(m + n8) bytes, k16 = k rounded up to 16 and n8 = n
  *                    rounded up to 8; both give the same bits. */
 typedef enum {
@@ -120,8 +120,8 @@ int gemm_plain(const gemm_problem_t *p, void *stream);
  * Configurations whose k-tile is copied straight into LDS in 16-byte chunks
  * need k and n multiples of the chunk (16 bytes of elements), lda and ldb
  * likewise and 16-byte aligned A and B.  Any other problem runs them on
- * packed copies of its operands, rows padded to whole chunks (m, n and k at
- * least 444, FP32 m and n 1774, copies of at most 512 MB), or runs the
+ * packed copies of its operands, rows padded to whole chunks (m and n at
+ * least 157, FP32 1774, and k 444, copies of at most 512 MB), or runs the
  * register-staged configuration of the same tile size instead.
  * Configurations whose waves share out k (4 or 8 waves; for them
  * gemm_config_info's waves is the number of k ranges a workgroup takes) add a

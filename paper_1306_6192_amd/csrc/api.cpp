@@ -192,19 +192,21 @@ static int64_t presplit_bytes(const gemm_problem_t &p, int64_t *b_off) {
 }
 
 // The copies pay where each packed element is used often enough and the
-// register-staged tile is far behind: from about 512 rows, columns and k for
-// the 16- and 8-bit forms (ragged bfloat16 with the shortest output side in
-// [512, 1024): 0.74 to 1.67 times the speed of the best tile without copies,
-// above 2048 up to 2.4 times), from about 2048 rows and columns for FP32,
-// whose 4-byte direct loads already take any shape (0.9 to 1.09 times below).
-// The lines are where the tuner's measured points turn to 512 and to 2048,
-// so that all shapes of a point run the kind of launch that was measured for
-// it (with the lines at 512 and 2048 themselves the points' shapes just below
-// ran without copies, and 537 x 3262 x 5706 on their choice took 264 us; 64
-// on the choice measured with copies).
+// register-staged tile is far behind: for the 16- and 8-bit forms and
+// split-BF16x3 from about 192 rows and columns and 512 k (without copies /
+// best tile on copies, us: BF16 185x7863x7863 138 / 89, 369x3931x3931 55 / 42,
+// 185x1965x3931 24 / 26, 123x3931x3931 25 / 30; E4M3 369x7863x7863 121 / 64;
+// split 369x3931x3931 91 / 68; above 2048 rows and columns up to 2.4 times),
+// for FP32, whose 4-byte direct loads already take any shape, from about 2048
+// (0.9 to 1.09 times below).  Within the range the tuner's points decide.  The
+// lines are where the points turn to 192, 512 and 2048, so that all shapes of
+// a point run the kind of launch that was measured for it (with lines at 512
+// and 2048 themselves the points' shapes just below ran without copies, and
+// 537 x 3262 x 5706 on their choice took 264 us; 64 on the choice measured
+// with copies).
 // Bounded, since the workspace is kept: larger copies are left to the
 // register-staged tiles.
-static int64_t pack_min(int mode) { return mode == GEMM_MODE_F32 ? 1774 : 444; }
+static int64_t pack_min(int mode) { return mode == GEMM_MODE_F32 ? 1774 : 157; }
 static const int64_t kPackMaxBytes = (int64_t)512 << 20;
 
 static bool pack_plan(const gemm_problem_t &p, const KernelCfg &kc, PackPlan *plan) {

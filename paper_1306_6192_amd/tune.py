@@ -183,7 +183,7 @@ def measure_grid(mg, _lib, torch, mode, path, limit_s):
                 large = 2.0 * m * n * k > 2e9
                 first = sorted((grid_time(torch, stream, launcher(c, sp), 3, 1), c, sp)
                                for c, sp in grid_candidates(mg, mode, infos, m, n, k)
-                               if whole or not chunks[c] or min(m, n, k) >= 444)
+                               if whole or not chunks[c] or min(m, n) >= 157 and k >= 444)
                 close = [(c, sp) for t, c, sp in first[:12] if t < 1.25 * first[0][0] + 1]
                 fine = min((grid_time(torch, stream, launcher(c, sp), 4 if large else 8, 3), c, sp) for c, sp in close)
             row.append((fine[1], fine[2]))

@@ -78,9 +78,9 @@ def test_every_config_equals_the_first_on_nan_padded_operands(mode, m, n, k):
                 assert np.array_equal(got, want), (cfg, split, x.stride(), y.stride())
 
 
-# near the smallest sizes that are copied (444; FP32 1774), ragged in k,
+# near the smallest sizes that are copied (157, FP32 1774; k 444), ragged in k,
 # in n, in both; whole chunks on a misaligned base
-PACKED = [(444, 445, 447), (512, 513, 515), (600, 520, 513), (515, 1000, 520), (520, 528, 528)]
+PACKED = [(157, 445, 447), (500, 157, 444), (512, 513, 515), (600, 520, 513), (515, 1000, 520), (520, 528, 528)]
 
 
 @pytest.mark.parametrize("m,n,k", PACKED)
@@ -90,7 +90,7 @@ def test_copied_operands_give_the_same_bits(mode, m, n, k):
     copied to aligned rows.  Also without an explicit configuration, and
     through the allocation-free entry point."""
     if mode == mg.MODE_F32:
-        m, n, k = m + 1330, n + 1330, k
+        m, n, k = m + 1617, n + 1617, k
     log(f"packed {_lib.MODE_NAMES[mode]} {(m, n, k)}")
     a, b = operands(mode, m, n, k, seed=m + n + k)
     views = ((a, b), (in_nan(a, mode, 1, 2), b), (a, in_nan(b, mode, 3, 2)), (in_nan(a, mode, 5, 1), in_nan(b, mode, 1, 1)))
