@@ -358,8 +358,10 @@ int upload_plan(const GroupPlan &plan, hipStream_t s, const void **dev_out) {
         if (st->host[b]) MG_HIP(hipHostFree(st->host[b]));
         st->host[b] = nullptr;
         st->bytes[b] = 0;
-        MG_HIP(hipHostMalloc(&st->host[b], std::max<size_t>(bytes, 4096), hipHostMallocDefault));
-        st->bytes[b] = std::max<size_t>(bytes, 4096);
+        // (freeing one waits for the whole device: room for the next larger plans)
+        const size_t room = std::max<size_t>(2 * bytes, 65536);
+        MG_HIP(hipHostMalloc(&st->host[b], room, hipHostMallocDefault));
+        st->bytes[b] = room;
     }
     plan_image_write(plan, st->host[b]);
     MG_HIP(launch_upload(db->ptr, st->host[b], (int64_t)bytes, s));
