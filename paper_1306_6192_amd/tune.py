@@ -131,10 +131,23 @@ def grid_time(torch, stream, launch, reps, rounds):
     return best
 
 
+def k_ranges(mg, mode, info, k, split):
+    """The k ranges that a split-K factor gives at `k`: whole grains (32 k for
+    FP32 and split-BF16x3, 64 for BF16 and F16, 128 for FP8) each.  A factor
+    that the waves along k of a small tile take costs nothing and stands."""
+    if split <= info["waves"] and (info["BM"] < 64 or info["BM"] * info["BN"] == 4096 and info["waves"] == 8):
+        return split
+    grain = {mg.MODE_F32: 32, mg.MODE_SPLIT_BF16X3: 32, mg.MODE_F8E4M3: 128}.get(mode, 64)
+    grains = -(-k // grain)
+    return -(-grains // -(-grains // min(split, grains)))
+
+
 def grid_candidates(mg, mode, infos, m, n, k):
     """(configuration, split) pairs worth timing: no 256-wide tile on a
     dimension of at most half of it, no split into ranges below 32 k, slabs of
-    at most 64 MB, large outputs without large splits."""
+    at most 64 MB, large outputs without large splits.  The split is the number
+    of ranges it makes at this k: a factor that has fewer grains to deal out
+    here would make more at the point's larger k."""
     for c, info in enumerate(infos):
         if (info["BM"] >= 256 and m <= 128) or (info["BN"] >= 256 and n <= 128):
             continue
@@ -142,11 +155,13 @@ def grid_candidates(mg, mode, infos, m, n, k):
             continue
         if info["BM"] * info["BN"] <= 4096 and m * n > 1 << 24:
             continue
-        split = 1
+        split, last = 1, 0
         while split <= 64 and (split == 1 or k // split >= 32):
             if split > 1 and split * m * n * 4 > 64e6 or split > 4 and m * n > 1 << 21:
                 break
-            yield c, split
+            if k_ranges(mg, mode, info, k, split) != last:
+                last = k_ranges(mg, mode, info, k, split)
+                yield c, last
             split *= 2
 
 
