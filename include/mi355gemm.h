@@ -111,8 +111,13 @@ typedef struct gemm_problem {
  * workspace (one per device and stream, grown on demand, kept until the
  * process ends; at most 512 MB of it packed copies) also holds the
  * split-BF16x3 operand copies and the packed copies of ragged operands (see
- * gemm_plain_cfg).  Under stream capture a workspace that is too small is
- * replaced, not freed: graphs captured before keep theirs. */
+ * gemm_plain_cfg).
+ * Work captured into a graph, of this and of every other entry point that has
+ * a workspace (gemm_grouped's plan included), gets one that belongs to the
+ * graph: later calls on the stream neither use nor free it, so the graph may
+ * be replayed on any stream beside them, and it is freed by a library call
+ * after the graph and its executables are destroyed.  Two executables
+ * instantiated from one capture share it: the caller orders their replays. */
 int gemm_plain(const gemm_problem_t *p, void *stream);
 
 /* As gemm_plain with an explicit tile configuration (index into

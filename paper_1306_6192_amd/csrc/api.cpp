@@ -1,12 +1,15 @@
 // C-ABI of the plain product, operand preparation, comparison reduction and
 // diagnostics.  Argument validation happens here, before any HIP call.
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
+#include <vector>
 
 #include "host.hpp"
 
@@ -347,35 +350,8 @@ int enqueue_plain(const gemm_problem_t &p, int cfg, int split, void *ws, hipStre
 // ---------------------------------------------------------------------------
 // Device buffers.
 
-// Buffers replaced while their stream was being captured: graphs captured
-// before may hold their addresses, so they stay allocated.
-static std::mutex g_retired_mu;
-static std::vector<void *> g_retired;
-
 int DevBuf::ensure(size_t need, hipStream_t s) {
     if (need <= bytes) return GEMM_OK;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        cap = hipStreamCaptureStatusNone;
-    }
-    const bool capturing = cap == hipStreamCaptureStatusActive;
-    // under capture an allocation (which enqueues nothing) needs the relaxed
-    // mode, and a stream that is being captured cannot be waited for
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    if (capturing) MG_HIP(hipThreadExchangeStreamCaptureMode(&mode));
-    struct Restore {
-        hipStreamCaptureMode *mode;
-        ~Restore() {
-            if (mode) (void)hipThreadExchangeStreamCaptureMode(mode);
-        }
-    } restore{capturing ? &mode : nullptr};
-    if (ptr && capturing) {
-        std::lock_guard<std::mutex> lk(g_retired_mu);
-        g_retired.push_back(ptr);
-        ptr = nullptr;
-        bytes = 0;
-    }
     if (ptr) {
         MG_HIP(hipStreamSynchronize(s));
         MG_HIP(hipFree(ptr));
@@ -400,7 +376,7 @@ void DevBuf::release() {
 }
 
 struct StreamWs {
-    std::mutex mu;   // held by the caller from ensure() to the enqueue of the work that uses a slot
+    std::mutex mu;   // held by the caller from stream_workspace() to the enqueue of the work that uses a slot
     DevBuf slot[4];
 };
 static std::mutex g_ws_mu;
@@ -415,7 +391,128 @@ static StreamWs *stream_ws(hipStream_t s) {
     return w;
 }
 
-DevBuf *stream_workspace(hipStream_t s, int slot) { return &stream_ws(s)->slot[slot]; }
+// ---------------------------------------------------------------------------
+// Buffers of captured work.  A graph may be replayed at any time and on any
+// stream, unordered with the calls made on the stream it was captured on, which
+// use, grow and free that stream's workspace.  So captured work gets buffers of
+// its own: one per (capture, stream, slot), larger ones beside the smaller ones
+// that earlier nodes hold, each owned by a user object of the graph, which HIP
+// releases with the last of the graph and the executables made of it.
+struct CaptureBuf {
+    unsigned long long capture;
+    hipStream_t stream;
+    int slot;              // kStagingSlot: pinned host memory, one per call
+    void *ptr = nullptr;
+    size_t bytes = 0;
+    std::atomic<bool> gone{false};
+};
+static const int kStagingSlot = -1;
+static std::mutex g_capture_mu;
+static std::vector<CaptureBuf *> g_capture;
+static std::atomic<int> g_capture_gone{0};
+
+// The user object's destructor: it may make no HIP call, so the buffer is only
+// marked; free_gone() frees it.
+static void capture_gone(void *p) {
+    static_cast<CaptureBuf *>(p)->gone.store(true);
+    g_capture_gone.fetch_add(1);
+}
+
+// Allocating and freeing while a stream is being captured (both enqueue
+// nothing) need the relaxed mode.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// Free the buffers of graphs that are gone (hipFree waits for the device, so
+// for a last replay that is still running).
+static void free_gone() {
+    if (g_capture_gone.load() == 0) return;
+    std::vector<CaptureBuf *> dead;
+    {
+        std::lock_guard<std::mutex> lk(g_capture_mu);
+        const auto keep = std::partition(g_capture.begin(), g_capture.end(), [](CaptureBuf *b) { return !b->gone.load(); });
+        dead.assign(keep, g_capture.end());
+        g_capture.erase(keep, g_capture.end());
+        g_capture_gone.fetch_sub((int)dead.size());
+    }
+    RelaxedCapture relaxed;
+    for (CaptureBuf *b : dead) {
+        (void)(b->slot == kStagingSlot ? hipHostFree(b->ptr) : hipFree(b->ptr));
+        delete b;
+    }
+}
+
+static bool capture_of(hipStream_t s, unsigned long long *id, hipGraph_t *graph) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamGetCaptureInfo_v2(s, &st, id, graph, nullptr, nullptr) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st == hipStreamCaptureStatusActive;
+}
+
+static int capture_buffer(unsigned long long id, hipGraph_t graph, hipStream_t s, int slot, size_t need, void **out) {
+    if (slot != kStagingSlot) {
+        std::lock_guard<std::mutex> lk(g_capture_mu);
+        for (CaptureBuf *b : g_capture)
+            if (!b->gone.load() && b->capture == id && b->stream == s && b->slot == slot && b->bytes >= need) {
+                *out = b->ptr;
+                return GEMM_OK;
+            }
+    }
+    RelaxedCapture relaxed;
+    std::unique_ptr<CaptureBuf> b(new CaptureBuf());
+    b->capture = id;
+    b->stream = s;
+    b->slot = slot;
+    b->bytes = (std::max<size_t>(need, 65536) + 255) / 256 * 256;
+    const hipError_t e = slot == kStagingSlot ? hipHostMalloc(&b->ptr, b->bytes, hipHostMallocDefault)
+                                              : hipMalloc(&b->ptr, b->bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(GEMM_ENOMEM, "workspace allocation of %zu bytes failed", b->bytes);
+    }
+    hipUserObject_t owner = nullptr;
+    if (hipUserObjectCreate(&owner, b.get(), capture_gone, 1, hipUserObjectNoDestructorSync) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)(slot == kStagingSlot ? hipHostFree(b->ptr) : hipFree(b->ptr));
+        return fail(GEMM_EHIP, "a captured graph's workspace has no owner");
+    }
+    // from here on the owner's release marks the buffer and free_gone() frees it
+    void *ptr = b->ptr;
+    {
+        std::lock_guard<std::mutex> lk(g_capture_mu);
+        g_capture.push_back(b.release());
+    }
+    if (hipGraphRetainUserObject(graph, owner, 1, hipGraphUserObjectMove) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipUserObjectRelease(owner, 1);
+        return fail(GEMM_EHIP, "a captured graph does not take its workspace");
+    }
+    *out = ptr;
+    return GEMM_OK;
+}
+
+int stream_workspace(hipStream_t s, int slot, size_t need, void **out) {
+    free_gone();
+    unsigned long long id = 0;
+    hipGraph_t graph = nullptr;
+    if (capture_of(s, &id, &graph)) return capture_buffer(id, graph, s, slot, need, out);
+    DevBuf &b = stream_ws(s)->slot[slot];
+    const int rc = b.ensure(need, s);
+    *out = b.ptr;
+    return rc;
+}
+
+int capture_staging(hipStream_t s, size_t bytes, void **out) {
+    *out = nullptr;
+    unsigned long long id = 0;
+    hipGraph_t graph = nullptr;
+    return capture_of(s, &id, &graph) ? capture_buffer(id, graph, s, kStagingSlot, bytes, out) : GEMM_OK;
+}
 
 std::unique_lock<std::mutex> lock_stream_workspaces(hipStream_t s) {
     return std::unique_lock<std::mutex>(stream_ws(s)->mu);
@@ -515,8 +612,7 @@ static int plain_common(const gemm_problem_t *p, int cfg, int split, void *strea
         int64_t need = plain_ws_bytes(*p, cfg, split, true);
         if (need > 0) {
             ws_lock = lock_stream_workspaces(s);
-            DevBuf *b = stream_workspace(s, 0);
-            rc = b->ensure((size_t)need, s);
+            rc = stream_workspace(s, 0, (size_t)need, &ws);
             if (rc == GEMM_ENOMEM) {
                 // without the packed copies (the register-staged tiles give
                 // the same bits)
@@ -524,11 +620,10 @@ static int plain_common(const gemm_problem_t *p, int cfg, int split, void *strea
                 if (less < need) {
                     clear_error();
                     pack = false;
-                    rc = less > 0 ? b->ensure((size_t)less, s) : GEMM_OK;
+                    rc = less > 0 ? stream_workspace(s, 0, (size_t)less, &ws) : GEMM_OK;
                 }
             }
             if (rc != GEMM_OK) return rc;
-            ws = b->ptr;
         }
     }
     return enqueue_plain(*p, cfg, split, ws, s, pack);
@@ -622,10 +717,10 @@ int gemm_quantize_e4m3(const float *x, int64_t count, uint8_t *q, float *scale_o
     if (count > 0 && overlaps(x, (size_t)count * 4, q, (size_t)count)) return fail(GEMM_EINVAL, "buffers overlap");
     hipStream_t s = (hipStream_t)stream;
     std::unique_lock<std::mutex> ws_lock = lock_stream_workspaces(s);
-    DevBuf *b = stream_workspace(s, 2);
-    int rc = b->ensure(4096, s);
+    void *ws = nullptr;
+    int rc = stream_workspace(s, 2, 4096, &ws);
     if (rc != GEMM_OK) return rc;
-    MG_HIP(launch_quantize_e4m3(x, count, q, scale_out, static_cast<uint32_t *>(b->ptr), s));
+    MG_HIP(launch_quantize_e4m3(x, count, q, scale_out, static_cast<uint32_t *>(ws), s));
     return GEMM_OK;
 }
 
@@ -639,10 +734,10 @@ int gemm_errnorm(const float *C, int64_t ldc, const double *R, int64_t ldr, int6
     hipStream_t s = (hipStream_t)stream;
     const int nparts = 2048;
     std::unique_lock<std::mutex> ws_lock = lock_stream_workspaces(s);
-    DevBuf *b = stream_workspace(s, 2);
-    int rc = b->ensure(4096 + (size_t)nparts * 3 * sizeof(double), s);
+    void *ws = nullptr;
+    int rc = stream_workspace(s, 2, 4096 + (size_t)nparts * 3 * sizeof(double), &ws);
     if (rc != GEMM_OK) return rc;
-    double *partials = reinterpret_cast<double *>(static_cast<char *>(b->ptr) + 4096);
+    double *partials = reinterpret_cast<double *>(static_cast<char *>(ws) + 4096);
     MG_HIP(launch_errnorm(C, ldc, R, ldr, m, n, out3, partials, nparts, s));
     return GEMM_OK;
 }

@@ -337,9 +337,18 @@ static std::map<std::pair<int, hipStream_t>, HostStage *> g_stage;
 
 int upload_plan(const GroupPlan &plan, hipStream_t s, const void **dev_out) {
     const size_t bytes = plan_image_bytes(plan);
-    DevBuf *db = stream_workspace(s, 1);
-    int rc = db->ensure(std::max<size_t>(bytes, 256), s);
+    void *image = nullptr, *staging = nullptr;
+    int rc = stream_workspace(s, 1, std::max<size_t>(bytes, 256), &image);
+    if (rc == GEMM_OK) rc = capture_staging(s, bytes, &staging);
     if (rc != GEMM_OK) return rc;
+    *dev_out = image;
+    if (staging) {
+        // a captured upload reads the plan at every replay: memory of the
+        // graph, which no later call writes
+        plan_image_write(plan, staging);
+        MG_HIP(launch_upload(image, staging, (int64_t)bytes, s));
+        return GEMM_OK;
+    }
     int dev = 0;
     (void)hipGetDevice(&dev);
     HostStage *st;
@@ -364,9 +373,8 @@ int upload_plan(const GroupPlan &plan, hipStream_t s, const void **dev_out) {
         st->bytes[b] = room;
     }
     plan_image_write(plan, st->host[b]);
-    MG_HIP(launch_upload(db->ptr, st->host[b], (int64_t)bytes, s));
+    MG_HIP(launch_upload(image, st->host[b], (int64_t)bytes, s));
     MG_HIP(hipEventRecord(st->ev[b], s));
-    *dev_out = db->ptr;
     return GEMM_OK;
 }
 

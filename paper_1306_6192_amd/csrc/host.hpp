@@ -96,11 +96,17 @@ struct DevBuf {
     void release();
 };
 
-// Per-stream library workspace (split-K slabs, grouped descriptors).
-DevBuf *stream_workspace(hipStream_t s, int slot);
+// The library workspace of a stream (slot 0: split-K slabs and operand copies,
+// 1: grouped descriptors, 2: reductions' partial results), at least `need`
+// bytes: the stream's own, grown on demand, or, while the stream is being
+// captured, one that belongs to the captured graph and is freed after it.
+int stream_workspace(hipStream_t s, int slot, size_t need, void **out);
+// Pinned host memory that belongs to the graph `s` is being captured into, a
+// new block for each call; null where the stream is not being captured.
+int capture_staging(hipStream_t s, size_t bytes, void **out);
 
 // Serialises host-side use of one (device, stream)'s workspaces: a caller
-// holds it from a workspace's ensure() until the work that reads the
+// holds it from stream_workspace() until the work that reads the
 // workspace is enqueued, so that a caller on another host thread using the
 // same stream cannot free and replace the buffer in between.
 std::unique_lock<std::mutex> lock_stream_workspaces(hipStream_t s);
