@@ -58,6 +58,17 @@ const at::Tensor *plain_tensor(PyObject *o) {
     return &t;
 }
 
+// The mode argument: exactly an int that names one (no error is left behind by
+// one that does not fit).
+bool mode_arg(PyObject *o, int *mode) {
+    if (!PyLong_CheckExact(o)) return false;
+    int over = 0;
+    const long v = PyLong_AsLongAndOverflow(o, &over);
+    if (over || v < 0 || v >= GEMM_NUM_MODES) return false;
+    *mode = (int)v;
+    return true;
+}
+
 // A row-major matrix as the Python layer accepts it.
 bool matrix(const at::Tensor &t) {
     return t.dim() == 2 && !(t.size(0) > 0 && t.size(1) > 1 && t.stride(1) != 1);
@@ -108,16 +119,16 @@ PyObject *result(int rc, PyObject *given, const at::Tensor &out) {
 PyObject *fast_gemm(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
     HANDLE_TH_ERRORS
     if (nargs != 6 || !g_plain || modes_active()) Py_RETURN_NONE;
-    if (!PyLong_CheckExact(args[3]) || !PyFloat_CheckExact(args[4]) || !PyFloat_CheckExact(args[5])) Py_RETURN_NONE;
+    int mode = 0;
+    if (!mode_arg(args[3], &mode) || !PyFloat_CheckExact(args[4]) || !PyFloat_CheckExact(args[5])) Py_RETURN_NONE;
     const at::Tensor *A = plain_tensor(args[0]), *B = plain_tensor(args[1]);
-    const long mode = PyLong_AsLong(args[3]);
-    if (!A || !B || !matrix(*A) || !matrix(*B) || !type_ok(A->scalar_type(), (int)mode) ||
-        !type_ok(B->scalar_type(), (int)mode) || A->size(1) != B->size(0))
+    if (!A || !B || !matrix(*A) || !matrix(*B) || !type_ok(A->scalar_type(), mode) ||
+        !type_ok(B->scalar_type(), mode) || A->size(1) != B->size(0))
         Py_RETURN_NONE;
     const at::Tensor C = output(args[2], *A, A->size(0), B->size(1), c10::ScalarType::Float);
     if (!C.defined()) Py_RETURN_NONE;
     gemm_problem_t p;
-    p.mode = (int32_t)mode;
+    p.mode = mode;
     p.flags = 0;
     p.m = A->size(0);
     p.n = B->size(1);
@@ -166,9 +177,9 @@ PyObject *fast_same(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
 // convert(x, mode)
 PyObject *fast_convert(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
     HANDLE_TH_ERRORS
-    if (nargs != 2 || !g_convert || modes_active() || !PyLong_CheckExact(args[1])) Py_RETURN_NONE;
+    int mode = 0;
+    if (nargs != 2 || !g_convert || modes_active() || !mode_arg(args[1], &mode)) Py_RETURN_NONE;
     const at::Tensor *x = plain_tensor(args[0]);
-    const long mode = PyLong_AsLong(args[1]);
     if (!x || x->scalar_type() != c10::ScalarType::Float || !x->is_contiguous() ||
         (mode != GEMM_MODE_BF16 && mode != GEMM_MODE_F16))
         Py_RETURN_NONE;
@@ -181,7 +192,7 @@ PyObject *fast_convert(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
     const int64_t count = x->numel();
     int rc;
     Py_BEGIN_ALLOW_THREADS
-    rc = g_convert((const float *)src, count, (int32_t)mode, (void *)dst, s);
+    rc = g_convert((const float *)src, count, mode, (void *)dst, s);
     Py_END_ALLOW_THREADS
     return result(rc, Py_None, out);
     END_HANDLE_TH_ERRORS

@@ -158,3 +158,15 @@ def test_calls_run_on_the_current_stream():
     assert not out.any()
     g.replay()
     assert np.array_equal(bits(out), want)
+
+
+@pytest.mark.parametrize("mode", [1 << 32, (1 << 32) + mg.MODE_BF16, 1 << 70, -1])
+def test_a_mode_outside_32_bits_is_refused(mode):
+    """By the layer itself, as a mode it does not know."""
+    log(f"fastcall mode {mode}")
+    a = torch.rand((4, 4), device="cuda")
+    for x in (a, a.to(torch.bfloat16)):
+        with pytest.raises(KeyError):
+            mg.gemm(x, x.clone(), mode=mode)
+    with pytest.raises(KeyError):
+        mg.convert(a, mode)
