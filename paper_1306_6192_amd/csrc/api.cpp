@@ -244,13 +244,13 @@ int effective_cfg(const gemm_problem_t &p, int cfg) {
     int count = 0;
     const KernelCfg *t = configs(p.mode, &count);
     if (!t || cfg < 0 || cfg >= count || cfg_eligible(p, t[cfg])) return cfg;
-    // a fused configuration's k ranges stay in one launch where its tile size
-    // has an any-shape fused form
-    for (int fused = t[cfg].fused ? 1 : 0; fused >= 0; --fused)
-        for (int c = 0; c < count; ++c)
-            if (t[c].chunk == 0 && !t[c].presplit && (t[c].fused != 0) == (fused != 0) && t[c].bm == t[cfg].bm &&
-                t[c].bn == t[cfg].bn)
-                return c;
+    // the any-shape form with as many waves along k (every fused configuration
+    // has one, so its k ranges stay in one launch without slabs, whatever the
+    // operands' strides and alignment; 0: the register-staged tile)
+    for (int c = 0; c < count; ++c)
+        if (t[c].chunk == 0 && !t[c].presplit && t[c].fused == t[cfg].fused && t[c].bm == t[cfg].bm &&
+            t[c].bn == t[cfg].bn)
+            return c;
     // no such tile size: the smallest larger one
     int best = 0;
     for (int c = 0; c < count; ++c) {

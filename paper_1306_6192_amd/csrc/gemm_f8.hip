@@ -24,6 +24,7 @@ static const KernelCfg kTable[] = {
     make_fused<Lp2Cfg<GEMM_MODE_F8E4M3, 64, 64, 2, 1, 1, 64, 16, 32, 8>, 2, 16>(),
     make_fused<Lp2Cfg<GEMM_MODE_F8E4M3, 32, 64, 2, 1, 1, 64, 0, 32, 4>, 2>(),
     make_fused<Lp2Cfg<GEMM_MODE_F8E4M3, 32, 64, 2, 1, 1, 64, 0, 32, 8>, 2>(),
+    make_fused<Lp2Cfg<GEMM_MODE_F8E4M3, 64, 64, 2, 1, 1, 64, 0, 32, 8>, 2>(),
 };
 
 const KernelCfg *lp_configs_f8(int *count) {

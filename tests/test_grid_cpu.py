@@ -126,3 +126,56 @@ def test_slabs_are_bounded_by_fewer_ranges(tmp_path):
     for (_, m, n, _), (cfg, split) in zip(shapes, lookups(f, shapes)):
         slab = (m * n + 3) // 4 * 16
         assert cfg == 6 and split == min(16, max(1, (64 << 20) // slab)), (m, n, split)
+
+
+WS = """
+import ctypes, json, sys
+sys.path.insert(0, %r)
+from paper_1306_6192_amd import _lib
+lib = _lib.load()
+def ws(mode, m, n, k, off):     # the addresses are not touched
+    w = ctypes.c_uint64()
+    p = _lib.problem(mode, m, n, k, (1 << 40) + off, k, (1 << 41) + off, n, 1 << 42, n)
+    _lib.check(lib.gemm_plain_workspace_bytes(ctypes.byref(p), ctypes.byref(w)))
+    return w.value
+print(json.dumps([ws(*q) for q in json.loads(sys.argv[1])]))
+"""
+
+
+def workspaces(table, queries):
+    env = dict(os.environ, MI355GEMM_TUNE_FILE=str(table)) if table else None
+    r = subprocess.run([sys.executable, "-c", WS % ROOT, json.dumps(queries)], env=env, capture_output=True, text=True,
+                       timeout=120)
+    assert r.returncode == 0, r.stderr
+    return json.loads(r.stdout.strip().splitlines()[-1])
+
+
+def test_misaligned_operands_keep_the_waves_along_k(tmp_path):
+    """A chunked configuration with waves along k has an any-shape form with as
+    many: the ranges of a split factor up to them need no slabs on operands off
+    16-byte alignment either (the figure reported beyond what is used stops at
+    64 MB, so slabs that are used show above it).  k is below what is packed."""
+    import ctypes
+    lib = _lib.load()
+    info = (ctypes.c_int32 * 6)()
+    f = tmp_path / "t.jsonl"
+    m, n, k = 4096, 4096, 384
+    for mode in (_lib.MODE_F32, _lib.MODE_BF16, _lib.MODE_F16, _lib.MODE_F8E4M3):
+        for cfg in range(lib.gemm_num_configs(mode)):
+            _lib.check(lib.gemm_config_info(mode, cfg, info))
+            waves_along_k = info[0] == 32 or (info[0] == 64 and info[1] == 64 and info[3] == 8)
+            if not lib.gemm_config_chunk(mode, cfg) or not waves_along_k:
+                continue
+            f.write_text('{"mode": %d, "m": %d, "n": %d, "k": %d, "cfg": %d, "split": %d}\n' % (mode, m, n, k, cfg, info[3]))
+            size = _lib.ELEM_SIZE[mode]
+            assert max(workspaces(f, [(mode, m, n, k, off) for off in (0, size)])) <= _lib.NOALLOC_SCRATCH_BYTES, (mode, cfg)
+
+
+def test_misaligned_operands_need_no_more_slabs_than_the_array_holds():
+    """The shipped table on large flat outputs (below what is packed), aligned
+    and one element off: what the allocation-free entry point holds suffices."""
+    qs = [(mode, m, n, k, off * _lib.ELEM_SIZE[mode]) for mode in (_lib.MODE_F32, _lib.MODE_BF16, _lib.MODE_F16, _lib.MODE_F8E4M3)
+          for m in (1, 16, 40, 64, 96, 128, 156) for n in (8192, 32768, 131072, 1 << 20, 1 << 22)
+          for k in (256, 1024, 4096, 16384) for off in (0, 1)]
+    for q, w in zip(qs, workspaces(None, qs)):
+        assert w <= _lib.NOALLOC_SCRATCH_BYTES, (q, w)
