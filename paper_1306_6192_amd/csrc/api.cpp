@@ -262,6 +262,67 @@ int effective_cfg(const gemm_problem_t &p, int cfg) {
     return best;
 }
 
+// The tuner's choice for a product that cannot run it (chunked or pre-split,
+// and no operand copies): the split factor stands, since it fixes the bits, and
+// an any-shape configuration takes its place.  The one of the same tile size is
+// often far behind: large tiles suit 16-byte direct loads, small ones loads
+// through registers.  So up to three tiles per mode, by the 64x64 tiles and k
+// ranges per CU (smaller tiles fill more of the chip): `few` below `limit`,
+// `most` from 20 on, else `many`; others in the 16- and 8-bit modes where the
+// rows start at changing places against the 16-byte boundaries.  Over 200 ragged
+// and 210 misaligned products (m, n 16..16384, k 64..16384) they are within 1.04
+// to 1.05 of the best any-shape configuration at the same factor (geometric
+// means by mode; E4M3 misaligned 1.10), the tile of the same size 1.1 (FP32,
+// split-BF16x3) to 2.6.  us, same size / now: E4M3 700x8191x8191 786 / 422,
+// 1500x1500x1501 79 / 38, BF16 700x8191x8191 943 / 497, split-BF16x3
+// 1500x1500x1501 131 / 74.
+struct AnyShape {
+    int few, many, most;
+    double limit;
+};
+static const AnyShape kAnyF32 = {24, 25, 25, 20.0}, kAnySplit = {5, 2, 2, 6.0};
+static const AnyShape kAny16 = {6, 13, 13, 4.0}, kAny16Ragged = {24, 4, 13, 4.0};
+static const AnyShape kAny8 = {6, 11, 11, 4.0}, kAny8Ragged = {14, 4, 11, 3.0};
+
+static int any_shape_cfg(const gemm_problem_t &p, const KernelCfg *t, int cfg, int split) {
+    const int same = effective_cfg(p, cfg);
+    const int64_t es = (int64_t)elem_size(p.mode);
+    const bool ragged_rows = p.lda * es % 16 || p.ldb * es % 16;
+    const Launch L = make_launch(p, t[cfg], split);
+    // slabs where the choice itself needs none: at most what gemm_plain_noalloc
+    // holds, so that it serves the same products
+    const bool slabs_fit = L.ws_bytes > 0 || L.splits * L.P.split_stride * 4 <= GEMM_NOALLOC_SCRATCH_BYTES;
+    if (t[cfg].fused && !ragged_rows && p.mode != GEMM_MODE_F32_SPLIT_BF16X3) {
+        // small tiles with waves along k: the same with loads through registers,
+        // but for few of them over a long k, whose ranges are better spread over
+        // more workgroups, slabs included (us, in the workgroup / on slabs: FP32
+        // 375x320x7552 47 / 30, 338x512x7808 on 176 tiles 47.5 / 50.8; BF16
+        // 18x320x2528 18.1 / 11.5, 31x32x512 7.5 / 7.5; E4M3 70x704x4256 21.6 / 12.8)
+        const bool few = 2 * (int64_t)L.P.tiles_m * L.P.tiles_n <= num_cus();
+        if (!few || p.k < (p.mode == GEMM_MODE_F32 ? 2048 : 1024) || !slabs_fit) return same;
+        if (p.mode != GEMM_MODE_F32) return kAny16.few;
+        int c = same;
+        while (t[c - 1].bm == t[c].bm && t[c - 1].bn == t[c].bn && t[c - 1].chunk == 0) --c;   // fewest waves
+        return c;
+    }
+    if (!slabs_fit) return same;
+    const AnyShape &a = p.mode == GEMM_MODE_F32 ? kAnyF32
+                        : p.mode == GEMM_MODE_F32_SPLIT_BF16X3 ? kAnySplit
+                        : p.mode == GEMM_MODE_F8E4M3 ? (ragged_rows ? kAny8Ragged : kAny8)
+                                                     : (ragged_rows ? kAny16Ragged : kAny16);
+    const double per_cu = (double)((p.m + 63) / 64) * (double)((p.n + 63) / 64) * L.splits / num_cus();
+    return per_cu < a.limit ? a.few : per_cu < 20.0 ? a.many : a.most;
+}
+
+void plain_choose(const gemm_problem_t &p, bool pack, int *cfg, int *split) {
+    tuner_choose(p.mode, p.m, p.n, p.k, cfg, split);
+    int count = 0;
+    const KernelCfg *t = configs(p.mode, &count);
+    if (!t || *cfg < 0 || *cfg >= count || p.m == 0 || p.n == 0 || p.k == 0) return;
+    PackPlan plan;
+    if (!cfg_eligible(p, t[*cfg]) && !(pack && pack_plan(p, t[*cfg], &plan))) *cfg = any_shape_cfg(p, t, *cfg, *split);
+}
+
 int64_t plain_ws_bytes(const gemm_problem_t &p, int cfg, int split, bool pack) {
     int count = 0;
     const KernelCfg *t = configs(p.mode, &count);
@@ -597,7 +658,8 @@ int gemm_config_chunk(int32_t mode, int32_t cfg) {
     return t[cfg].chunk;
 }
 
-static int plain_common(const gemm_problem_t *p, int cfg, int split, void *stream) {
+// `chosen`: (cfg, split) is plain_choose's, not the caller's.
+static int plain_common(const gemm_problem_t *p, int cfg, int split, bool chosen, void *stream) {
     int rc = validate(p);
     if (rc != GEMM_OK) return rc;
     hipStream_t s = (hipStream_t)stream;
@@ -614,8 +676,8 @@ static int plain_common(const gemm_problem_t *p, int cfg, int split, void *strea
             ws_lock = lock_stream_workspaces(s);
             rc = stream_workspace(s, 0, (size_t)need, &ws);
             if (rc == GEMM_ENOMEM) {
-                // without the packed copies (the register-staged tiles give
-                // the same bits)
+                // without the packed copies (same bits)
+                if (chosen) plain_choose(*p, false, &cfg, &split);
                 const int64_t less = plain_ws_bytes(*p, cfg, split, false);
                 if (less < need) {
                     clear_error();
@@ -634,8 +696,8 @@ int gemm_plain(const gemm_problem_t *p, void *stream) {
     int rc = validate(p);
     if (rc != GEMM_OK) return rc;
     int cfg = 0, split = 1;
-    tuner_choose(p->mode, p->m, p->n, p->k, &cfg, &split);
-    return plain_common(p, cfg, split, stream);
+    plain_choose(*p, true, &cfg, &split);
+    return plain_common(p, cfg, split, true, stream);
 }
 
 int gemm_plain_cfg(const gemm_problem_t *p, int32_t cfg, int32_t split_k, void *stream) {
@@ -647,7 +709,7 @@ int gemm_plain_cfg(const gemm_problem_t *p, int32_t cfg, int32_t split_k, void *
     configs(p->mode, &count);
     if (count == 0) return fail(GEMM_EUNSUPPORTED, "mode %d has no kernels", p->mode);
     if (cfg < 0 || cfg >= count) return fail(GEMM_EINVAL, "config %d out of range [0,%d)", cfg, count);
-    return plain_common(p, cfg, split_k, stream);
+    return plain_common(p, cfg, split_k, false, stream);
 }
 
 int gemm_plain_workspace_bytes(const gemm_problem_t *p, uint64_t *bytes_out) {
@@ -658,7 +720,7 @@ int gemm_plain_workspace_bytes(const gemm_problem_t *p, uint64_t *bytes_out) {
     if (rc != GEMM_OK) return rc;
     if (p->m == 0 || p->n == 0 || p->k == 0) return GEMM_OK;
     int cfg = 0, split = 1;
-    tuner_choose(p->mode, p->m, p->n, p->k, &cfg, &split);
+    plain_choose(*p, true, &cfg, &split);
     *bytes_out = (uint64_t)plain_ws_reported(*p, cfg, split, true);
     return GEMM_OK;
 }
@@ -677,11 +739,12 @@ int gemm_plain_noalloc(const gemm_problem_t *p, void *stream) {
         int count = 0;
         configs(p->mode, &count);
         if (count == 0) return fail(GEMM_EUNSUPPORTED, "mode %d has no kernels", p->mode);
-        tuner_choose(p->mode, p->m, p->n, p->k, &cfg, &split);
+        plain_choose(*p, true, &cfg, &split);
         int64_t need = plain_ws_bytes(*p, cfg, split, true);
         if (need > GEMM_NOALLOC_SCRATCH_BYTES) {
             // without the packed copies (same bits)
             pack = false;
+            plain_choose(*p, false, &cfg, &split);
             need = plain_ws_bytes(*p, cfg, split, false);
         }
         if (need > GEMM_NOALLOC_SCRATCH_BYTES)

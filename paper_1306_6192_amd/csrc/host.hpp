@@ -59,6 +59,9 @@ bool cfg_eligible(const gemm_problem_t &p, const KernelCfg &kc);
 bool cfg_runs(const gemm_problem_t &p, const KernelCfg &kc);
 bool presplit_shape_ok(int64_t n, int64_t k);
 int split_grain(int mode);
+// The tuner's choice for the problem, its configuration replaced where neither
+// the problem as it stands nor (`pack`) its packed copies can run it.
+void plain_choose(const gemm_problem_t &p, bool pack, int *cfg, int *split);
 int effective_cfg(const gemm_problem_t &p, int cfg);
 
 // Workspace bytes the (cfg, split) choice uses for this problem: split-K slabs

@@ -66,7 +66,7 @@ static uint64_t footprint_of(const gemm_problem_t &p, int executor) {
     uint64_t fp = (uint64_t)p.m * p.k * es + (uint64_t)p.k * p.n * es + (uint64_t)p.m * p.n * 4;
     if (executor == 2 && p.m > 0 && p.n > 0 && p.k > 0) {
         int c = 0, sp = 1;
-        tuner_choose(p.mode, p.m, p.n, p.k, &c, &sp);
+        plain_choose(p, false, &c, &sp);
         fp += (uint64_t)plain_ws_reported(p, c, sp, false);
     }
     return fp;
@@ -198,7 +198,7 @@ int Server::launch_batch(Slot &s, std::vector<Request *> &b) {
     if (cfg.executor == 2) {
         for (Request *r : b) {
             int c = 0, sp = 1;
-            tuner_choose(r->p.mode, r->p.m, r->p.n, r->p.k, &c, &sp);
+            plain_choose(r->p, false, &c, &sp);
             const int64_t need = plain_ws_bytes(r->p, c, sp);
             if (need > 0) {
                 int rc = s.ws.ensure((size_t)need, s.stream);
