@@ -379,9 +379,10 @@ typedef struct gemm_serve_stats {
 
 /* Admission footprint of a request under the batched executors (0, 1):
  * bytes(A) + bytes(B) + 4*m*n (grouped launches and a batch of one use no
- * workspace).  The plain-launch executor (2) admits each request by that
- * plus gemm_plain_workspace_bytes(p) less any packed copies (it makes none),
- * the workspace of its plain launch. */
+ * workspace).  The plain-launch executor (2) admits each request by that plus
+ * the workspace its plain launch uses: gemm_plain_workspace_bytes(p) less the
+ * packed copies (it makes none) and less slabs that the chosen configuration
+ * leaves unused. */
 int gemm_serve_footprint(const gemm_problem_t *p, uint64_t *bytes_out);
 int gemm_serve_create(const gemm_serve_config_t *cfg, void **server_out);
 /* Enqueue one request (copied); returns a monotonic ticket.  GEMM_ENOMEM if

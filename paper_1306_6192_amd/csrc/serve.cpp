@@ -67,7 +67,7 @@ static uint64_t footprint_of(const gemm_problem_t &p, int executor) {
     if (executor == 2 && p.m > 0 && p.n > 0 && p.k > 0) {
         int c = 0, sp = 1;
         plain_choose(p, false, &c, &sp);
-        fp += (uint64_t)plain_ws_reported(p, c, sp, false);
+        fp += (uint64_t)plain_ws_bytes(p, c, sp);
     }
     return fp;
 }
