@@ -108,8 +108,9 @@ typedef struct gemm_problem {
  * and split-K factor come from the tuning table (shape-keyed); split-K
  * partial sums go to a library-owned workspace and are summed in a fixed
  * order, so a given (mode, m, n, k) always produces the same bits.  The
- * workspace (one per device and stream, grown on demand, kept until the
- * process ends; at most 512 MB of it packed copies) also holds the
+ * workspace (one per device and stream, grown on demand to at least twice its
+ * size, or 256 MB more, and kept until the process ends; at most 512 MB of what
+ * a product needs are packed copies) also holds the
  * split-BF16x3 operand copies and the packed copies of ragged operands (see
  * gemm_plain_cfg).
  * Work captured into a graph, of this and of every other entry point that has

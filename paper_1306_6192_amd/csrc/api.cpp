@@ -411,23 +411,26 @@ int enqueue_plain(const gemm_problem_t &p, int cfg, int split, void *ws, hipStre
 // ---------------------------------------------------------------------------
 // Device buffers.
 
-int DevBuf::ensure(size_t need, hipStream_t s) {
+int DevBuf::ensure(size_t need, hipStream_t s, bool room) {
     if (need <= bytes) return GEMM_OK;
+    const size_t last = bytes;
     if (ptr) {
         MG_HIP(hipStreamSynchronize(s));
         MG_HIP(hipFree(ptr));
         ptr = nullptr;
         bytes = 0;
     }
-    size_t sz = std::max<size_t>(need, 1 << 20);
-    sz = (sz + 255) / 256 * 256;
-    if (hipMalloc(&ptr, sz) != hipSuccess) {
+    const size_t roomy = room ? std::max(need, std::min(2 * last, last + ((size_t)256 << 20))) : need;
+    for (size_t want : {roomy, need}) {
+        const size_t sz = (std::max<size_t>(want, 1 << 20) + 255) / 256 * 256;
+        if (hipMalloc(&ptr, sz) == hipSuccess) {
+            bytes = sz;
+            return GEMM_OK;
+        }
         ptr = nullptr;
         (void)hipGetLastError();
-        return fail(GEMM_ENOMEM, "workspace allocation of %zu bytes failed", sz);
     }
-    bytes = sz;
-    return GEMM_OK;
+    return fail(GEMM_ENOMEM, "workspace allocation of %zu bytes failed", need);
 }
 
 void DevBuf::release() {
@@ -563,7 +566,7 @@ int stream_workspace(hipStream_t s, int slot, size_t need, void **out) {
     hipGraph_t graph = nullptr;
     if (capture_of(s, &id, &graph)) return capture_buffer(id, graph, s, slot, need, out);
     DevBuf &b = stream_ws(s)->slot[slot];
-    const int rc = b.ensure(need, s);
+    const int rc = b.ensure(need, s, true);
     *out = b.ptr;
     return rc;
 }

@@ -95,7 +95,7 @@ void tuner_record_grouped_eff(int mode, double eff, int variant);
 struct DevBuf {
     void *ptr = nullptr;
     size_t bytes = 0;
-    int ensure(size_t need, hipStream_t s);
+    int ensure(size_t need, hipStream_t s, bool room = false);
     void release();
 };
 

@@ -81,3 +81,31 @@ def test_the_array_holds_what_is_used(mode, m, n, k):
         assert np.array_equal(host(out), want)
     if mode == mg.MODE_SPLIT_BF16X3:
         assert oracle.relerr(want, oracle.gemm(A, B)) <= 1e-5
+
+
+def test_growing_products_replace_the_workspace_seldom():
+    """Twenty ever larger ragged products (copies of 4 to 34 MB) on a stream
+    that has no workspace yet: the buffer is replaced at every doubling, not at
+    every product."""
+    log("workspace growth")
+    hip = ctypes.CDLL("libamdhip64.so")
+    handle = ctypes.c_void_p()
+    assert hip.hipStreamCreateWithFlags(ctypes.byref(handle), 1) == 0
+    stream = torch.cuda.ExternalStream(handle.value)
+    mode = mg.MODE_BF16
+    cfg = next(c for c in range(mg.num_configs(mode)) if mg.config_chunk(mode, c))
+    sizes = range(1001, 3001, 100)
+    x = torch.randn((3001, 3001), device="cuda").to(torch.bfloat16)
+    out = torch.empty((3001, 3001), device="cuda")
+    ops = [(x.view(-1)[:n * n].view(n, n), out.view(-1)[:n * n].view(n, n)) for n in sizes]
+    torch.cuda.synchronize()
+    free = [torch.cuda.mem_get_info()[0]]
+    for a, c in ops:
+        mg.gemm(a, a, out=c, mode=mode, cfg=cfg, split_k=1, stream=stream)
+        torch.cuda.synchronize()
+        free.append(torch.cuda.mem_get_info()[0])
+    replaced = sum(a != b for a, b in zip(free, free[1:]))
+    assert replaced <= 6, free
+    a, c = ops[-1]
+    want = host(mg.gemm(a, a, mode=mode, cfg=cfg, split_k=1))
+    assert np.array_equal(host(c), want)
