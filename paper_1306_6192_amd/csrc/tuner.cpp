@@ -65,6 +65,8 @@ static int grid_point(int64_t d) {
     return 2 * (b - 5) + (2 * sq < 3 * base ? 0 : sq < 3 * base ? 1 : 2);
 }
 
+static int64_t point_dim(int i) { return (int64_t)(i % 2 ? 3 : 2) << (4 + i / 2); }
+
 // Whether k and n are whole 16-byte chunks of the mode's asynchronous-copy
 // tiles (split-BF16x3: whether n is, for its operand copies).
 static int grid_class(int mode, int64_t n, int64_t k) {
@@ -143,6 +145,36 @@ static void load_env_locked() {
     if (env && *env) (void)load_file_locked(env);
 }
 
+static GridChoice grid_at(int mode, int cl, int im, int in, int ik) {
+    GridChoice c = g_grid[mode][cl][im][in][ik];
+    // binary16 runs on the same tiles as bfloat16, at the same rates
+    if (c.cfg < 0 && mode == GEMM_MODE_F16) c = g_grid[GEMM_MODE_BF16][cl][im][in][ik];
+    return c;
+}
+
+// The k ranges that a split factor gives (make_launch), with slabs of at most
+// 64 MB, as at the measured points: larger products of a point's range take
+// fewer ranges (147x7866x7815 in split-BF16x3 with 14 of its point's 16: 186 us;
+// with one, 606).
+static int bounded_split(const KernelCfg &kc, int64_t m, int64_t n, int split) {
+    const int in_wg = std::max(1, kc.fused);
+    const int64_t slab = ((m * n + 3) / 4 * 4) * 4;
+    return split > in_wg && split * slab > 67108864 ? std::max(in_wg, (int)(67108864 / slab)) : split;
+}
+
+static int64_t k_ranges(int mode, int64_t k, int split) {
+    const int64_t grains = std::max<int64_t>(1, (k + split_grain(mode) - 1) / split_grain(mode));
+    const int64_t per = (grains + std::min<int64_t>(split, grains) - 1) / std::min<int64_t>(split, grains);
+    return (grains + per - 1) / per;
+}
+
+// Workgroups over those that are resident at once.
+static double rounds_of(const KernelCfg &kc, int64_t m, int64_t n, int64_t ranges) {
+    const double tiles = (double)((m + kc.bm - 1) / kc.bm) * (double)((n + kc.bn - 1) / kc.bn);
+    return tiles * (double)(kc.fused ? (ranges + kc.fused - 1) / kc.fused : ranges) /
+           ((double)num_cus() * std::max(1, kc.wg_per_cu));
+}
+
 void tuner_choose(int mode, int64_t m, int64_t n, int64_t k, int *cfg, int *split) {
     {
         std::lock_guard<std::mutex> lk(g_mu);
@@ -161,21 +193,38 @@ void tuner_choose(int mode, int64_t m, int64_t n, int64_t k, int *cfg, int *spli
         }
         if (mode_known(mode)) {
             const int cl = grid_class(mode, n, k), im = grid_point(m), in = grid_point(n), ik = grid_point(k);
-            GridChoice c = g_grid[mode][cl][im][in][ik];
-            // binary16 runs on the same tiles as bfloat16, at the same rates
-            if (c.cfg < 0 && mode == GEMM_MODE_F16) c = g_grid[GEMM_MODE_BF16][cl][im][in][ik];
+            const GridChoice c = grid_at(mode, cl, im, in, ik);
             if (c.cfg >= 0) {
                 int count = 0;
-                const KernelCfg &kc = configs(mode, &count)[c.cfg];
+                const KernelCfg *t = configs(mode, &count);
                 *cfg = c.cfg;
-                *split = c.split;
-                // slabs of at most 64 MB, as at the measured points: larger products
-                // of a point's range take fewer ranges (147x7866x7815 in
-                // split-BF16x3 with 14 of its point's 16: 186 us; with one, 606)
-                const int in_wg = std::max(1, kc.fused);
-                const int64_t slab = ((m * n + 3) / 4 * 4) * 4;
-                if (*split > in_wg && *split * slab > 67108864)
-                    *split = std::max(in_wg, (int)(67108864 / slab));
+                *split = bounded_split(t[c.cfg], m, n, c.split);
+                // A shape just above its point may need one more, mostly empty
+                // round of workgroups than the point did (up to 1.6 rounds; 2 and
+                // more gain nothing).  It takes the configuration of the next
+                // point along the dimension in which it is further above, if
+                // that has fewer rounds here, the same k ranges (so the same
+                // bits) and another tile.  119 of 9000 drawn shapes (m, n, k of
+                // 32..4096, and 1..256 by 1024..8192) do: 0.80 of their time on
+                // average, one more than 1.07 (E4M3 3046x147x115 10.5 -> 6.2 us,
+                // FP32 2305x3990x3498 846 -> 651; 572x580x2397 29.4 -> 35.8).
+                // With other ranges or along both dimensions: up
+                // to 1.4 and 2.9 times slower.  Split-BF16x3's points stay level.
+                const int64_t ranges = k_ranges(mode, k, *split);
+                const double here = rounds_of(t[c.cfg], m, n, ranges);
+                const double above_m = (double)m / point_dim(im), above_n = (double)n / point_dim(in);
+                const bool by_m = above_m >= above_n;
+                if (mode != GEMM_MODE_F32_SPLIT_BF16X3 && here <= 1.6 && std::max(above_m, above_n) > 1.0 &&
+                    (by_m ? im : in) + 1 < GRID_POINTS &&
+                    std::ceil(here) > std::ceil(rounds_of(t[c.cfg], point_dim(im), point_dim(in), ranges))) {
+                    const GridChoice up = grid_at(mode, cl, im + by_m, in + !by_m, ik);
+                    const int up_split = up.cfg >= 0 ? bounded_split(t[up.cfg], m, n, up.split) : 0;
+                    if (up.cfg >= 0 && rounds_of(t[up.cfg], m, n, ranges) < here && k_ranges(mode, k, up_split) == ranges &&
+                        (t[up.cfg].bm != t[c.cfg].bm || t[up.cfg].bn != t[c.cfg].bn || t[up.cfg].waves != t[c.cfg].waves)) {
+                        *cfg = up.cfg;
+                        *split = up_split;
+                    }
+                }
                 return;
             }
         }

@@ -179,3 +179,54 @@ def test_misaligned_operands_need_no_more_slabs_than_the_array_holds():
           for k in (256, 1024, 4096, 16384) for off in (0, 1)]
     for q, w in zip(qs, workspaces(None, qs)):
         assert w <= _lib.NOALLOC_SCRATCH_BYTES, (q, w)
+
+
+def test_a_mostly_empty_round_takes_the_next_points_tile(tmp_path):
+    """Above the workgroups that are resident at once (256 CUs), where the point
+    was not: the configuration of the next point along the dimension further
+    above, with the same k ranges; otherwise the point's own."""
+    f = tmp_path / "t.jsonl"
+    n17 = len(POINTS)
+    # E4M3, ragged: configuration 15 (32x64, one workgroup per CU) at n = 2048, m = 256; up in m 14 (two per CU)
+    # with the same ranges, up in n 6 with one; at m = 384 (nearest 384), up in m, 14 with other ranges
+    rows = [line(_lib.MODE_F8E4M3, 0, 6, 12, [(15, 2)] * n17), line(_lib.MODE_F8E4M3, 0, 7, 12, [(14, 2)] * n17),
+            line(_lib.MODE_F8E4M3, 0, 6, 13, [(6, 1)] * n17), line(_lib.MODE_F8E4M3, 0, 8, 12, [(14, 1)] * n17),
+            line(_lib.MODE_SPLIT_BF16X3, 0, 6, 12, [(19, 2)] * n17), line(_lib.MODE_SPLIT_BF16X3, 0, 7, 12, [(18, 2)] * n17)]
+    f.write_text("".join(rows))
+    Q, S = _lib.MODE_F8E4M3, _lib.MODE_SPLIT_BF16X3
+    k = 255
+    shapes = [(Q, 256, 2047, k), (Q, 250, 2051, k), (Q, 257, 2047, k), (Q, 300, 2049, k), (Q, 257, 2070, k), (Q, 240, 2241, k),
+              (Q, 256, 2047, 100), (Q, 257, 2047, 100), (S, 300, 2049, k)]
+    # in one round; below the point in m and above in n: up in n, other ranges; up in m; further above in n; k of one range
+    # (its neighbour's factor gives one range too); split-BF16x3: none
+    want = [(15, 2), (15, 2), (14, 2), (14, 2), (15, 2), (15, 2), (15, 2), (14, 2), (19, 2)]
+    assert lookups(f, shapes) == want
+
+
+def test_the_next_points_tile_keeps_the_k_ranges(tmp_path):
+    """Over the shipped table: a drawn shape's split factor gives the k ranges of
+    its own point's."""
+    import random
+    grid = {}
+    with open(os.path.join(ROOT, "paper_1306_6192_amd", "tuning", "mi355x.jsonl")) as fh:
+        for ln in fh:
+            if ln.startswith('{"grid"'):
+                d = json.loads(ln)
+                grid[(d["grid"], d["whole"], d["m"], d["n"])] = [tuple(map(int, c.split(":"))) for c in d["choices"].split()]
+    table = tmp_path / "grid_only.jsonl"
+    table.write_text("".join(line(*key, row) for key, row in grid.items()))
+    r = random.Random(4)
+    shapes = [(r.choice((0, 1, 3)), *(int(math.exp(r.uniform(math.log(17), math.log(4096)))) for _ in range(3))) for _ in range(4000)]
+    grain, moved = {0: 32, 1: 64, 3: 128}, 0
+
+    def ranges(mode, k, split):
+        g = -(-k // grain[mode])
+        return -(-g // -(-g // min(split, g)))
+
+    for (mode, m, n, k), (cfg, split) in zip(shapes, lookups(table, shapes)):
+        c = 16 // _lib.ELEM_SIZE[mode]
+        own = grid[(mode, int(n % c == 0 and k % c == 0), nearest(m), nearest(n))][nearest(k)]
+        moved += cfg != own[0]
+        if own[1] * m * n * 4 <= _lib.NOALLOC_SCRATCH_BYTES:
+            assert ranges(mode, k, split) == ranges(mode, k, own[1]), (mode, m, n, k, cfg, split, own)
+    assert 0 < moved < 200, moved
