@@ -23,13 +23,7 @@ __device__ __forceinline__ u32x4 pack_chunk(const uint8_t *row, uint32_t row_byt
     if (have >= 16) return ld16(row + 16 * (int64_t)c);
     if (row_bytes >= 16) {
         // the row's last 16 bytes, its last `have` bytes moved to the front
-        const u32x4 v = ld16(row + row_bytes - 16);
-        unsigned __int128 w;
-        __builtin_memcpy(&w, &v, 16);
-        w >>= 8 * (16 - have);
-        u32x4 r;
-        __builtin_memcpy(&r, &w, 16);
-        return r;
+        return shift_down16(ld16(row + row_bytes - 16), 16 - have);
     }
     uint8_t b[16];
 #pragma unroll

@@ -12,6 +12,16 @@ __device__ __forceinline__ u32x4 ld16(const void *p) {
     return v;
 }
 
+// Bytes `by` (0 .. 15) and on of v, moved to the front, zeros behind them.
+__device__ __forceinline__ u32x4 shift_down16(const u32x4 &v, int by) {
+    unsigned __int128 w;
+    __builtin_memcpy(&w, &v, 16);
+    w >>= 8 * by;
+    u32x4 r;
+    __builtin_memcpy(&r, &w, 16);
+    return r;
+}
+
 // Store the accumulators of one wave tile to C (row stride ldc) or to a
 // split-K partial slab.  MFMA 32x32 result layout: lane l, register r holds
 // row 8*(r/4) + 4*(l/32) + r%4 of the block; the kernels feed lane l%32 = jj

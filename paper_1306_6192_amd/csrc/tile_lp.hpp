@@ -188,6 +188,13 @@ __device__ __forceinline__ u32x4 lp_load16(const uint8_t *__restrict__ base, int
         const uint8_t *p = base + ((int64_t)r * ld + c) * ESZ;
         if (c + N <= Cn) {
             v = ld16(p);
+        } else if (ESZ < 4 && Cn >= N) {
+            // the row's last 16 bytes, its last Cn - c elements moved to the
+            // front: one load where 8 or 16 are behind as many branches, which
+            // every wave of a tile at the matrices' ends takes (E4M3
+            // 1502x1350x461 14.8 -> 9.3 us, 172 drawn ragged products 1.09 times
+            // faster, bfloat16 1.04; four float32 loads are not slower)
+            if (c < Cn) v = shift_down16(ld16(p - (c + N - Cn) * ESZ), (c + N - Cn) * ESZ);
         } else {
             uint8_t b[16];
 #pragma unroll
