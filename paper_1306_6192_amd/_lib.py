@@ -150,14 +150,29 @@ def load():
     return _lib
 
 
+class _GeneralPath:
+    """Stands in for the native call path where that is not built: every call is
+    left to the Python layer's own path, which runs the same library."""
+
+    @staticmethod
+    def gemm(*args):
+        return None
+
+    gemm_same = convert = quantize = gemm
+
+
 def fastcall():
     """The native call path of the Python layer's small entry points, bound to
-    the loaded library (raises if it is not built, like :func:`load`)."""
+    the loaded library."""
     global _fast
     if _fast is None:
         import torch  # noqa: F401  (its libraries are the module's)
         lib = load()
-        from . import _fastcall
+        try:
+            from . import _fastcall
+        except ImportError:
+            _fast = _GeneralPath
+            return _fast
         _fastcall.bind(*(ctypes.cast(getattr(lib, name), c_void_p).value
                          for name in ("gemm_plain", "gemm_plain_f64", "gemm_plain_c32", "gemm_convert_f32",
                                       "gemm_quantize_e4m3")))

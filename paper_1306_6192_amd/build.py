@@ -5,7 +5,7 @@ compiled for gfx950 only and linked into one shared library that exports the
 C-ABI declared in ``include/mi355gemm.h``.  The compiler's per-kernel
 resource report (registers, scratch, occupancy, LDS) is kept in
 ``_build/kernel_resources.txt``.  ``_fastcall.so``, the Python layer's native
-call path, is built beside the library.  A kernel that spills registers to scratch
+call path, is built beside the library where torch's headers are.  A kernel that spills registers to scratch
 memory fails the build, since every tile is sized to fit its register budget.
 """
 from __future__ import annotations
@@ -73,13 +73,22 @@ def _compile(src: str, verbose: bool):
 
 def _build_fastcall(verbose: bool) -> None:
     """The Python layer's native call path (host code against torch's C++
-    headers; it is handed the library's entry points when it is loaded)."""
+    headers; it is handed the library's entry points when it is loaded).  Left
+    out, as the Python layer works without it, where torch, its headers or a
+    host compiler is missing."""
+    import importlib.util
+    import shutil
     import sysconfig
 
+    cxx = os.environ.get("CXX", "g++")
+    found = importlib.util.find_spec("torch")
+    tdir = os.path.dirname(found.origin) if found and found.origin else ""
+    if not shutil.which(cxx) or not os.path.exists(os.path.join(tdir, "include", "ATen", "ATen.h")):
+        print("native call path not built: it needs torch, its headers and a host compiler", file=sys.stderr)
+        return
     import torch
-    tdir = os.path.dirname(torch.__file__)
     tmp = FASTCALL + ".tmp"
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
            "-DUSE_ROCM", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
            "-I", os.path.join(tdir, "include"), "-I", os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
