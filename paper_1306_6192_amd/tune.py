@@ -3,7 +3,7 @@ the library loads at start-up.
 
     python -m paper_1306_6192_amd.tune [--out PATH] [--what exact,grid,grouped]
 
-Three kinds of entries (each chosen by the library's own timing):
+Kinds of entries (each chosen by the library's own timing):
 
 * ``exact``: the configuration and split-K factor of each benchmark shape
   (``gemm_tune``: every legal configuration and split-K factor, timed with
@@ -14,6 +14,9 @@ Three kinds of entries (each chosen by the library's own timing):
   16-byte chunks and for ragged ones (FP32, BF16 -- which F16 shares -- E4M3
   and split-BF16x3), consulted for every shape without an exact or bucket
   entry; each candidate is timed as a graph of back-to-back launches;
+* ``plain-buckets`` (not in the shipped table): the measurement of ``exact`` on
+  one representative shape per log2 bucket of (m, n, k) (``gemm_tune_bucket``),
+  consulted before the grid;
 * ``grouped``: the plain tile (128x128 or 64x64) per bucket for a problem
   launched alone (``gemm_tune_grouped``), and per mode the grouped kernel
   variant (one tile at three workgroups per CU, or two tiles with a cost
@@ -284,7 +287,7 @@ def main(argv=None):
                 return 1
         _lib.check(lib.gemm_tuner_load(args.out.encode()))
     buckets = bucket_shapes(mg)
-    for kind, entry in (("grouped", lib.gemm_tune_grouped),):
+    for kind, entry in (("plain-buckets", lib.gemm_tune_bucket), ("grouped", lib.gemm_tune_grouped)):
         if kind not in what:
             continue
         for mode, shapes in buckets.items():
