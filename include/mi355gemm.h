@@ -127,8 +127,10 @@ int gemm_plain(const gemm_problem_t *p, void *stream);
  * need k and n multiples of the chunk (16 bytes of elements), lda and ldb
  * likewise and 16-byte aligned A and B.  Any other problem runs them on
  * packed copies of its operands, rows padded to whole chunks (m and n at
- * least 157, FP32 1774, and k 444, copies of at most 512 MB), or runs the
- * register-staged configuration of the same tile size instead.
+ * least 157, FP32 1774, and k 444, copies of at most 512 MB), or runs an
+ * any-shape configuration of the same tile size and waves along k instead
+ * (gemm_plain: the any-shape one that suits the problem, at the same split
+ * factor and so with the same bits).
  * Configurations whose waves share out k (4 or 8 waves; for them
  * gemm_config_info's waves is the number of k ranges a workgroup takes) add a
  * split factor of up to that in the workgroup, without slabs.  Split-K
@@ -343,8 +345,9 @@ int gemm_tune_grouped(int32_t mode, int64_t m, int64_t n, int64_t k, void *strea
 int gemm_tune_grouped_mix(const gemm_problem_t *ps, int32_t count, void *stream);
 /* The (cfg, split_k) gemm_plain would use for this shape: the exact entry,
  * else the bucket entry, else the choice of the nearest point of the table's
- * measured grid (shapes of whole 16-byte chunks and ragged ones apart), else
- * the cost model. */
+ * measured grid (shapes of whole 16-byte chunks and ragged ones apart; where a
+ * shape just above its point needs another round of workgroups, the next
+ * point's configuration at the same k ranges), else the cost model. */
 int gemm_tuner_lookup(int32_t mode, int64_t m, int64_t n, int64_t k, int32_t *cfg, int32_t *split_k);
 int gemm_tuner_load(const char *path);
 int gemm_tuner_save(const char *path);

@@ -185,8 +185,8 @@ struct PackPlan {
     int64_t bytes() const { return a_bytes + b_bytes; }
 };
 
-// Bytes of the interleaved operand copies of the pre-split path (A' then B',
-// each 256-byte aligned).
+// Bytes of the operand copies of the pre-split path (A's hi and lo parts, then
+// B's, each 256-byte aligned).
 static int64_t presplit_bytes(const gemm_problem_t &p, int64_t *b_off) {
     const int64_t k16 = (p.k + 15) / 16 * 16, n8 = (p.n + 7) / 8 * 8;
     const int64_t a = ((int64_t)p.m * 2 * k16 * 2 + 255) / 256 * 256;
@@ -216,7 +216,7 @@ static bool pack_plan(const gemm_problem_t &p, const KernelCfg &kc, PackPlan *pl
     if ((kc.chunk == 0 && !kc.presplit) || cfg_eligible(p, kc)) return false;
     if (p.m < pack_min(p.mode) || p.n < pack_min(p.mode) || p.k < 444) return false;
     if (kc.presplit) {
-        // ragged n: the interleaved copies are made all the same, B's rows
+        // ragged n: the pre-split copies are made all the same, B's rows
         // padded to eight columns (enqueue_plain makes and sizes them)
         int64_t b_off = 0;
         *plan = PackPlan();

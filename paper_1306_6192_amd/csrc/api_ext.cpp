@@ -1,5 +1,6 @@
 // C-ABI entry points of the binary64 and complex-float products and of the
-// element-wise matrix addition (plain launches, no split-K, no workspace).
+// element-wise matrix addition: one launch each, no workspace (k is at most
+// shared out among the waves of a workgroup).
 #include <algorithm>
 #include <cmath>
 #include <cstring>

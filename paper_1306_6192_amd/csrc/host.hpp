@@ -53,7 +53,7 @@ int enqueue_plain(const gemm_problem_t &p, int cfg, int split, void *ws, hipStre
 // Whether the problem's shape, strides and alignment meet the configuration's
 // chunk requirement, and the configuration actually run for it: a chunked
 // configuration the problem does not meet is replaced by the any-shape one of
-// the same tile size (both sum every element in the same order).
+// the same tile size and waves along k (both sum every element in the same order).
 bool cfg_eligible(const gemm_problem_t &p, const KernelCfg &kc);
 // ... or can run on packed copies of the operands.
 bool cfg_runs(const gemm_problem_t &p, const KernelCfg &kc);
@@ -91,7 +91,9 @@ int tuner_grouped_variant(int mode);
 void tuner_record_grouped_eff(int mode, double eff, int variant);
 
 // A device buffer owned by the library that grows on demand.  Growth waits
-// for `s` to drain before freeing the old allocation.
+// for `s` to drain before freeing the old allocation, so with `room` a larger
+// buffer has some for the next (twice the last size, at most 256 MB more; just
+// what is needed where the device has no such room).
 struct DevBuf {
     void *ptr = nullptr;
     size_t bytes = 0;

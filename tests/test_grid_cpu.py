@@ -230,3 +230,19 @@ def test_the_next_points_tile_keeps_the_k_ranges(tmp_path):
         if own[1] * m * n * 4 <= _lib.NOALLOC_SCRATCH_BYTES:
             assert ranges(mode, k, split) == ranges(mode, k, own[1]), (mode, m, n, k, cfg, split, own)
     assert 0 < moved < 200, moved
+
+
+def test_any_shape_tiles_of_the_rule():
+    """The configurations that stand in for one that cannot run (any_shape_cfg
+    names them by index): any-shape, of the tiles that were measured."""
+    import ctypes
+    lib = _lib.load()
+    info = (ctypes.c_int32 * 6)()
+    half = {6: (64, 64, 64, 4), 13: (128, 128, 32, 4), 24: (32, 64, 32, 4), 4: (128, 64, 64, 4)}
+    want = {_lib.MODE_F32: {24: (64, 64, 32, 4), 25: (128, 128, 16, 4)}, _lib.MODE_BF16: half, _lib.MODE_F16: half,
+            _lib.MODE_F8E4M3: {6: (64, 64, 128, 4), 11: (128, 128, 64, 4), 14: (32, 64, 64, 4), 4: (128, 64, 128, 4)},
+            _lib.MODE_SPLIT_BF16X3: {5: (64, 64, 32, 4), 2: (128, 128, 32, 4)}}
+    for mode, tiles in want.items():
+        for cfg, tile in tiles.items():
+            _lib.check(lib.gemm_config_info(mode, cfg, info))
+            assert lib.gemm_config_chunk(mode, cfg) == 0 and tuple(info[:4]) == tile, (mode, cfg, list(info))
