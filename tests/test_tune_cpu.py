@@ -1,13 +1,18 @@
 """The tuning program's kinds of entries, without a GPU: which of the library's
 measuring entry points each kind calls."""
-import importlib
+import importlib.util
+import os
 
 import pytest
 
 torch = pytest.importorskip("torch")
 import paper_1306_6192_amd as mg  # noqa: E402
 
-tune = importlib.import_module("paper_1306_6192_amd.tune")
+# (as a program is run: an import as the package's submodule would take the name
+# of the package's function `tune`)
+_spec = importlib.util.spec_from_file_location("tuning_program", os.path.join(os.path.dirname(mg.__file__), "tune.py"))
+tune = importlib.util.module_from_spec(_spec)
+_spec.loader.exec_module(tune)
 
 
 class Recorder:
