@@ -143,3 +143,31 @@ def test_a_destroyed_graph_gives_its_workspace_back():
         free.append(torch.cuda.mem_get_info()[0])
     # ten graphs held 640 MB: less than two of them may be missing at the end
     assert free[1] - free[9] < 128 << 20, free
+
+
+def test_forked_streams_of_one_capture():
+    """Products on two streams of one capture, unordered with one another, have a
+    workspace each."""
+    log("capture, forked")
+    mode, sizes = mg.MODE_BF16, [(333, 463, 601), (401, 517, 777)]
+    cfg = copies_config(mode)
+    ops = [operands(mode, *s, seed=i) for i, s in enumerate(sizes)]
+    want = [host(mg.gemm(a, b, mode=mode, cfg=cfg, split_k=3)) for a, b in ops]
+    outs = [torch.empty(s[:2], device="cuda") for s in sizes]
+    side, fork = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        fork.wait_stream(side)
+        for _ in range(3):
+            mg.gemm(*ops[0], out=outs[0], mode=mode, cfg=cfg, split_k=3)
+            with torch.cuda.stream(fork):
+                mg.gemm(*ops[1], out=outs[1], mode=mode, cfg=cfg, split_k=3)
+        side.wait_stream(fork)
+    for _ in range(4):
+        for o in outs:
+            o.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        for o, w in zip(outs, want):
+            assert np.array_equal(host(o), w)
